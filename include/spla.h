@@ -191,8 +191,8 @@ enum {
                             with the rows of o_bar = phi(q) S_bar split over its workgroups */
   SPLA_PHASE_MERGE = 4,  /* merge of that pass, residual, RMSNorm, output */
   SPLA_PHASE_DECODE = 5, /* the single-launch decode kernel (all of phases 1-4) */
-  SPLA_PHASE_LINEAR = 6, /* chunked prefill: the chunkwise linear-attention kernel
-                            (o_bar of every query, S_bar and z_bar past the chunk) */
+  SPLA_PHASE_LINEAR = 6, /* chunked prefill: S_bar before each block of the chunk and
+                            S_bar and z_bar past it */
   SPLA_NUM_PHASES = 8
 };
 
@@ -200,9 +200,10 @@ enum {
  * recorded on the call's stream right before / after the launch(es) of phase
  * p. The phases a call records are given by spla_decode_phase_mask (plus
  * SPLA_PHASE_APPEND for spla_step_ex); the others record nothing. The chunked
- * prefill (spla_prefill_ex) records APPEND (the running unit statistics and
- * the rows and statistics of the chunk), LINEAR, SCORE, SELECT,
- * SPARSE and MERGE for every chunk, so with several chunks the events end up
+ * prefill (spla_prefill_ex) records APPEND (the units in progress, the rows
+ * and the statistics of the chunk), LINEAR, SCORE, SELECT, SPARSE and MERGE
+ * (empty unless groups are split) for every chunk, so with several chunks the
+ * events end up
  * bracketing the last one. */
 typedef struct spla_events {
   void* start[SPLA_NUM_PHASES];
@@ -337,13 +338,14 @@ int32_t spla_step(const spla_config* cfg, const spla_cache* cache, const void* k
  *  sel_idx:      device int32 [n_tokens][batch][Hkv][top_k] or NULL.
  *  workspace:    at least spla_prefill_workspace_bytes(cfg, n_tokens) bytes,
  *                256-byte aligned (no preparation needed).
- * bf16 shapes with G <= 8 run chunks of up to 32 positions through the
- * chunked kernels (Sec. 3.3 "Kernel Design": a chunkwise linear-attention
- * kernel for o_bar that also carries S_bar and z_bar past the chunk, and the
- * fused sparse kernel per query, after per-query scoring that reads each
- * statistics tile once per chunk and per-query top-k); other shapes (which
- * never decode in one launch) run the positions one at a time as spla_step
- * does, on the separate decode launches. n_tokens = 0 does nothing; tokens past max_seq_len
+ * bf16 shapes with G <= 8 run chunks of up to 1024 positions (as many as keep
+ * the chunk's block scores within 320 MB, at least 32) through the chunked
+ * kernels (Sec. 3.3 "Kernel Design": the global linear term from S_bar before
+ * each block of the chunk, block scores of every query on the matrix cores,
+ * per-query top-k, and the fused sparse kernel over groups of consecutive
+ * queries, which share the blocks that more than one of them selects); other
+ * shapes (which never decode in one launch) run the positions one at a time as
+ * spla_step does, on the separate decode launches. n_tokens = 0 does nothing; tokens past max_seq_len
  * are dropped as in spla_step (SPLA_DEVERR_CAPACITY) and the queries at those
  * positions decode over the full cache. */
 int32_t spla_prefill(const spla_config* cfg, const spla_cache* cache, int32_t n_tokens,

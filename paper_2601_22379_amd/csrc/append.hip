@@ -383,11 +383,17 @@ struct alignas(16) StateSmem {
   float z[4][D];              // per-wavefront sums of phi(k)
 };
 
+//
+// Chunk x holds new tokens x chunk_tokens .. + chunk_tokens - 1; with aligned,
+// those of the x-th block of the sequence from the append point's on (the
+// chunked prefill's partial of every block; chunk_tokens = B). New row r of
+// bh is element bh s_bh + r s_row of k_new and v_new, as in append_unit.
 template <int D>
 __global__ __launch_bounds__(256) void append_state_mfma_kernel(
     Dims m, const int32_t* __restrict__ seq_lens, const bf16_t* __restrict__ k_new,
     const bf16_t* __restrict__ v_new, int max_new, const int32_t* __restrict__ n_new, int n_chunks,
-    int chunk_tokens, float* __restrict__ part_s, float* __restrict__ part_z) {
+    int chunk_tokens, float* __restrict__ part_s, float* __restrict__ part_z, bool aligned,
+    int64_t s_bh, int64_t s_row) {
   constexpr int RT = D / 16;        // row tiles (coordinates j)
   constexpr int CT = D / 64;        // column tiles per wavefront
   __shared__ StateSmem<D> sm;
@@ -396,9 +402,12 @@ __global__ __launch_bounds__(256) void append_state_mfma_kernel(
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int li = lane & 15, lg = lane >> 4;
   bool clipped;
-  const int ne = appended_count(m, seq_lens[b], max_new, n_new, b, &clipped);
-  const int t0 = blockIdx.x * chunk_tokens;
-  const int t1 = min(t0 + chunk_tokens, ne);
+  const int L0 = seq_lens[b];
+  const int ne = appended_count(m, L0, max_new, n_new, b, &clipped);
+  const int tc = (int)blockIdx.x * chunk_tokens - (aligned ? L0 % chunk_tokens : 0);
+  const int t0 = max(tc, 0);
+  const int t1 = min(tc + chunk_tokens, ne);
+  if (aligned && t0 >= t1) return;  // a block without new tokens: its partial is not read
   afloatx4 acc[RT][CT];
 #pragma unroll
   for (int r = 0; r < RT; ++r)
@@ -407,8 +416,8 @@ __global__ __launch_bounds__(256) void append_state_mfma_kernel(
   float zacc[8];  // phi(k) of this lane's coordinates, summed over its tokens
 #pragma unroll
   for (int i = 0; i < 8; ++i) zacc[i] = 0.f;
-  const bf16_t* kb = k_new + (int64_t)bh * max_new * D;
-  const bf16_t* vb = v_new + (int64_t)bh * max_new * D;
+  const bf16_t* kb = k_new + (int64_t)bh * s_bh;
+  const bf16_t* vb = v_new + (int64_t)bh * s_bh;
   // wavefront w takes tokens 8 w .. 8 w + 7 of each 32-token step as NS
   // 16-byte loads per lane: LPR = D / 8 lanes per token, lane l holding
   // coordinates 8 (l % LPR) .. + 7 of token tok(s) (with two loads, tokens
@@ -423,8 +432,8 @@ __global__ __launch_bounds__(256) void append_state_mfma_kernel(
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int row = min(tt + tok(s), t1 - 1);
-      kx[s] = *reinterpret_cast<const uint4*>(kb + (int64_t)row * D + 8 * cl);
-      vx[s] = *reinterpret_cast<const uint4*>(vb + (int64_t)row * D + 8 * cl);
+      kx[s] = *reinterpret_cast<const uint4*>(kb + (int64_t)row * s_row + 8 * cl);
+      vx[s] = *reinterpret_cast<const uint4*>(vb + (int64_t)row * s_row + 8 * cl);
     }
   };
   // max / sum over the LPR lanes of a token (every lane gets the same bits)
@@ -1016,10 +1025,22 @@ __global__ void append_finish_kernel(Dims m, int32_t* __restrict__ seq_lens, int
   if (appended) appended[b] = n;
 }
 
-__global__ void fill_zero_kernel(uint32_t* __restrict__ p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0u;
+// Zeroes up to four buffers of 32-bit words (any may be empty), 16 bytes per
+// store where a buffer starts on a 16-byte boundary.
+struct ZeroSpans {
+  uint32_t* p[4];
+  int64_t n[4];  // words
+};
+__global__ __launch_bounds__(256) void fill_zero_kernel(ZeroSpans z) {
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int64_t n4 = reinterpret_cast<uintptr_t>(z.p[b]) % 16 == 0 ? z.n[b] / 4 : 0;
+    for (int64_t i = first; i < n4; i += step)
+      reinterpret_cast<uint4*>(z.p[b])[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int64_t i = 4 * n4 + first; i < z.n[b]; i += step) z.p[b][i] = 0u;
+  }
 }
 
 // ------------------------------------------------------------- launchers
@@ -1052,7 +1073,7 @@ static void state_partial(const Dims& m, const spla_cache& c, const void* k_new,
     hipLaunchKernelGGL((append_state_mfma_kernel<D>), dim3(ws.n_chunks, m.bh), dim3(256), 0, st,
                        m, c.seq_lens, (const bf16_t*)k_new, (const bf16_t*)v_new, max_new, n_new,
                        ws.n_chunks, ws.chunk_tokens, (float*)(base + ws.part_s),
-                       (float*)(base + ws.part_z));
+                       (float*)(base + ws.part_z), false, (int64_t)max_new * D, (int64_t)D);
   else
     hipLaunchKernelGGL((append_state_partial_kernel<T, D>), dim3(ws.n_chunks, m.bh), dim3(256), 0,
                        st, m, c.seq_lens, (const T*)k_new, (const T*)v_new, max_new, n_new,
@@ -1076,6 +1097,17 @@ hipError_t launch_append_state(const Dims& m, const spla_cache& c, const void* k
                      st, m, ws.n_chunks, (const float*)(base + ws.part_s),
                      (const float*)(base + ws.part_z), c.lin_state, c.lin_norm, nullptr, 0,
                      nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_block_states(const Dims& m, const spla_cache& c, const void* k_new,
+                               const void* v_new, int T, int n_blk, float* part_s, float* part_z,
+                               hipStream_t st) {
+  auto kern = m.d == 64 ? append_state_mfma_kernel<64> : append_state_mfma_kernel<128>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_blk, (unsigned)m.bh), dim3(256), 0, st, m,
+                     (const int32_t*)c.seq_lens, (const bf16_t*)k_new, (const bf16_t*)v_new, T,
+                     (const int32_t*)nullptr, n_blk, m.B, part_s, part_z, true, (int64_t)m.d,
+                     (int64_t)m.bh * m.d);
   return hipGetLastError();
 }
 
@@ -1144,13 +1176,27 @@ hipError_t launch_append_finish(const Dims& m, const spla_cache& c, int max_new,
   return hipGetLastError();
 }
 
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
-  const int64_t n = (int64_t)(bytes / 4);
-  if (n == 0) return hipSuccess;
-  int64_t blocks = ceil_div(n, 256);
-  if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (uint32_t*)p, n);
+static hipError_t fill_zero(const ZeroSpans& z, hipStream_t st) {
+  int64_t most = 0;
+  for (int b = 0; b < 4; ++b) most = z.n[b] > most ? z.n[b] : most;
+  if (most == 0) return hipSuccess;
+  int64_t blocks = ceil_div(most, 4 * 256);
+  if (blocks > 4096) blocks = 4096;
+  hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, st, z);
   return hipGetLastError();
+}
+
+hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
+  return fill_zero(ZeroSpans{{(uint32_t*)p, nullptr, nullptr, nullptr},
+                             {(int64_t)(bytes / 4), 0, 0, 0}}, st);
+}
+
+hipError_t launch_reset(const spla_cache& c, const size_t* bytes, hipStream_t st) {
+  return fill_zero(
+      ZeroSpans{{(uint32_t*)c.blk_stats, (uint32_t*)c.lin_state, (uint32_t*)c.lin_norm,
+                 (uint32_t*)c.seq_lens},
+                {(int64_t)bytes[2] / 4, (int64_t)bytes[3] / 4, (int64_t)bytes[4] / 4,
+                 (int64_t)bytes[5] / 4}}, st);
 }
 
 }  // namespace spla

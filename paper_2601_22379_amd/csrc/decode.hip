@@ -221,7 +221,7 @@ void decode_kernel(FusedArgs a) {
   if constexpr (G > 4) {  // two query heads per wavefront (merge_halves)
     const int g = 2 * (tid >> 6);
     if (g < G)
-      merge_head<bf16_t, D, true, false, true>(m, a.eps, a.flags, a.gamma, all_sel, L, rec,
+      merge_head<bf16_t, D, true, true>(m, a.eps, a.flags, a.gamma, all_sel, L, rec,
                                                a.n_wg, a.stride, a.out, bh, g);
   } else {
     for (int g = tid >> 6; g < G; g += 4)

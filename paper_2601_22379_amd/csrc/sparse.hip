@@ -22,11 +22,11 @@ __global__ __launch_bounds__(64) void merge_kernel(
     T* __restrict__ out) {
   const int bh = blockIdx.x;
   if (merge_halves(m.group))  // uniform: two query heads per workgroup
-    merge_head<T, D, false, false, true>(m, eps, flags, gamma, meta[bh * 4 + 1],
+    merge_head<T, D, false, true>(m, eps, flags, gamma, meta[bh * 4 + 1],
                                          meta[bh * 4 + 2], part + (int64_t)bh * n_rec * stride,
                                          n_rec, stride, out, bh, 2 * (int)blockIdx.y);
   else if (n_rec > 16)  // uniform: every record's loads in one batch (32 records)
-    merge_head<T, D, false, false, false, 16>(m, eps, flags, gamma, meta[bh * 4 + 1],
+    merge_head<T, D, false, false, 16>(m, eps, flags, gamma, meta[bh * 4 + 1],
                                               meta[bh * 4 + 2], part + (int64_t)bh * n_rec * stride,
                                               n_rec, stride, out, bh, (int)blockIdx.y);
   else
@@ -343,7 +343,7 @@ void sparse_mfma_kernel(
     float m_run = -INFINITY, l_run = 0.f;
     if (kv.n_valid > 0) sparse_mma<D, GC>(s, kv, sm, acc_o, m_run, l_run);
     sparse_record<D, false, GC>(m, acc_o, m_run, l_run, bh, x, (int)gridDim.x, r, sm, part,
-                                stride, -1);
+                                stride);
   } else {  // every workgroup makes its head's selection itself
     sparse_prologue<D, GC>(m, q, S, zbar, bh, x, (int)gridDim.x, r, sm);
     sparse_linear<D, GC>(m, S, bh, r, sm);

@@ -127,10 +127,7 @@ extern "C" int32_t spla_reset(const spla_config* cfg, const spla_cache* cache, v
   size_t b[SPLA_CACHE_NUM_BUFFERS];
   spla_cache_bytes(cfg, b);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  SPLA_TRY(spla::launch_fill_zero(cache->blk_stats, b[2], st));
-  SPLA_TRY(spla::launch_fill_zero(cache->lin_state, b[3], st));
-  SPLA_TRY(spla::launch_fill_zero(cache->lin_norm, b[4], st));
-  SPLA_TRY(spla::launch_fill_zero(cache->seq_lens, b[5], st));
+  SPLA_TRY(spla::launch_reset(*cache, b, st));
   return SPLA_OK;
 }
 
@@ -253,8 +250,10 @@ extern "C" int32_t spla_prefill_ex(const spla_config* cfg, const spla_cache* cac
   char* ob = static_cast<char*>(out);
   if (spla::use_chunked_prefill(m)) {
     const spla::PrefillWs L = spla::prefill_ws_layout(m, n_tokens);
-    for (int32_t c0 = 0; c0 < n_tokens; c0 += L.T) {
-      const int T = n_tokens - c0 < L.T ? n_tokens - c0 : L.T;
+    // chunks of about equal size
+    const int n_chunks = (n_tokens - 1) / L.T + 1, step = (n_tokens - 1) / n_chunks + 1;
+    for (int32_t c0 = 0; c0 < n_tokens; c0 += step) {
+      const int T = n_tokens - c0 < step ? n_tokens - c0 : step;
       SPLA_TRY(spla::launch_prefill_chunk(m, *cfg, *cache, T, kb + c0 * kv_step,
                                           vb + c0 * kv_step, qb + c0 * q_step, w,
                                           ob + c0 * q_step,

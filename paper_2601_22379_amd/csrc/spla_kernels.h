@@ -27,6 +27,12 @@ hipError_t launch_append_blocks(const Dims& m, const spla_cache& c, const void* 
 hipError_t launch_append_state(const Dims& m, const spla_cache& c, const void* k_new,
                                const void* v_new, int max_new, const int32_t* n_new,
                                const AppendWs& ws, char* wsbase, hipStream_t st);
+// phi(K)^T V (part_s [bh][n_blk][d][d]) and the sums of phi(K) (part_z
+// [bh][n_blk][d]) of the new tokens of each block that T new position-major
+// rows touch, from the block of the append point on (bf16)
+hipError_t launch_block_states(const Dims& m, const spla_cache& c, const void* k_new,
+                               const void* v_new, int T, int n_blk, float* part_s, float* part_z,
+                               hipStream_t st);
 // rows, block statistics and state partials of a bulk append in one pass over
 // the new keys and values (append_fusable shapes: bf16, d = 128, blocks as
 // the statistics units), then the state reduce, which also advances seq_lens;
@@ -48,6 +54,9 @@ hipError_t launch_append_finish(const Dims& m, const spla_cache& c, int max_new,
                                 const int32_t* n_new, hipStream_t st,
                                 int32_t* appended = nullptr);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t st);
+// zeroes the statistics, the state, its normaliser and the lengths in one
+// launch; bytes as spla_cache_bytes gives them
+hipError_t launch_reset(const spla_cache& c, const size_t* bytes, hipStream_t st);
 
 // score.hip: block scoring
 // the scoring launch with the selection folded in (score_selects shapes; in
@@ -77,7 +86,7 @@ hipError_t launch_sparse(const Dims& m, const spla_config& cfg, const spla_cache
 hipError_t launch_merge(const Dims& m, const spla_config& cfg, const float* rms_weight, void* out,
                         const DecodeWs& ws, char* wsbase, hipStream_t st);
 
-// prefill.hip: one chunk of at most kPrefillChunk positions of the chunked
+// prefill.hip: one chunk of at most ws.T positions of the chunked
 // causal prefill (use_chunked_prefill shapes); q, k_new, v_new, out and
 // sel_out point at the chunk's first position
 hipError_t launch_prefill_chunk(const Dims& m, const spla_config& cfg, const spla_cache& c,

@@ -222,29 +222,62 @@ SPLA_HD bool step_fusable(const Dims& m) {
 }
 
 // ---- chunked prefill workspace ------------------------------------------------
-constexpr int kPrefillChunk = 32;  // positions per chunk of the chunked prefill
-constexpr int kPrefillStepsPerWave = 8;  // 32-token steps per wavefront of its sparse pass
+// Positions per chunk: as many as keep the block masses of the chunk's queries
+// (e_vals) within kPrefillScoreBytes, between kPrefillMinChunk and
+// kPrefillMaxChunk. Long chunks fill the GPU (a chunk's launches take a few
+// microseconds each whatever it holds: 1000 positions of 4 x 8 units from an
+// empty cache took 233 us in two chunks against 4430 us in chunks of 32). At
+// 128K tokens and 4 x 8 units the limit gives chunks of 320 positions (256
+// positions in one chunk rather than two of 128 also saves the split groups'
+// records).
+constexpr int kPrefillMinChunk = 32, kPrefillMaxChunk = 1024;
+constexpr int64_t kPrefillScoreBytes = 320 << 20;
+constexpr int kPrefillFill = 512;   // group-pass workgroups to aim for (two per compute unit)
+constexpr int kPrefillMaxSplit = 16;  // workgroups that share one group's blocks at most
 
 // The chunked prefill covers the matrix-core shapes (bf16, G <= 8); the other
 // shapes run position by position (the single-token append, then a decode).
 SPLA_HD bool use_chunked_prefill(const Dims& m) { return use_mfma_sparse(m); }
 
+// Query positions per wavefront of its group pass: a power of two with at
+// most 16 query rows (the columns of a matrix-core tile). A workgroup takes
+// four times as many consecutive positions, aligned in the sequence, so that
+// a wavefront's positions lie in one block.
+SPLA_HD int prefill_wave_positions(int G) { return G <= 1 ? 16 : G <= 2 ? 8 : G <= 4 ? 4 : 2; }
+// Blocks, and groups of positions, that T consecutive tokens touch at most.
+SPLA_HD int prefill_blocks(const Dims& m, int T) { return (T + m.B - 2) / m.B + 1; }
+SPLA_HD int prefill_groups(const Dims& m, int T) {
+  const int qw = 4 * prefill_wave_positions(m.group);
+  return (T + qw - 2) / qw + 1;
+}
+// Workgroups sharing the blocks of one group: enough to fill the GPU, each
+// with at least four 32-token steps of one query's selection.
+SPLA_HD int prefill_splits(const Dims& m, int T) {
+  const int64_t groups = (int64_t)m.bh * prefill_groups(m, T);
+  int64_t n = ceil_div(kPrefillFill, groups);
+  const int64_t most = ceil_div((int64_t)m.k * (m.B / 32), 4);
+  n = n < most ? n : most;
+  return (int)(n < kPrefillMaxSplit ? n : kPrefillMaxSplit);
+}
+
 struct PrefillWs {
-  int T;            // positions per chunk
-  int nu_touch;     // statistics units that T consecutive tokens can touch
-  int n_wg;         // sparse workgroups per query (kPrefillStepsPerWave steps per wavefront)
+  int T;            // positions per chunk at most
   int part_stride;  // floats per record
-  int64_t ustat;    // f32 [bh][nu_touch][T][2][d]  running (mean, M2) of the touched units
-  int64_t e_vals;   // f32 [bh T][G][n_tiles*64]    per query, as the decode's
-  int64_t tile_part;  // f64 [bh T][G][n_tiles][2]
-  int64_t sel;      // i32 [bh T][k]
-  int64_t meta;     // i32 [bh T][4]
-  int64_t part;     // f32 [bh T][n_wg][part_stride]
-  int64_t obar;     // f32 [bh][T G][d]  o_bar of every query (row = position G + head)
-  int64_t zq;       // f32 [bh][T G]     <phi(q), z_bar> of every query
+  int64_t ell_part;   // f64 [bh][T][W][G]  log masses of the units in progress (W = ul / us)
+  int64_t e_vals;     // f32 [bh][T G][n_tiles*64]  per query row, as the decode's
+  int64_t tile_part;  // f64 [bh][T G][n_tiles][2]
+  int64_t sel;        // i32 [bh T][k]
+  int64_t near;       // i32 [1 + bh T]  queries whose selection is taken again: count, rows
+  int64_t part_s;     // f32 [bh][n_blk][d][d]  phi(K)^T V of each block the chunk touches
+  int64_t part_z;     // f32 [bh][n_blk][d]
+  int64_t s_hi, s_lo; // bf16 [bh][n_blk][d d]  S_bar before each block, operand order
+  int64_t z_pre;      // f32 [bh][n_blk][d]
+  int64_t part;       // f32 [bh T][n_split][part_stride]  records of split groups
   int64_t total;
 };
 
+// Every size grows with n_tokens, so a workspace for n positions serves every
+// smaller call.
 SPLA_HD PrefillWs prefill_ws_layout(const Dims& m, int n_tokens) {
   PrefillWs w;
   const int64_t A = SPLA_WORKSPACE_ALIGN;
@@ -254,21 +287,32 @@ SPLA_HD PrefillWs prefill_ws_layout(const Dims& m, int n_tokens) {
     off = align_up(off + bytes, A);
     return o;
   };
-  w.T = n_tokens < 1 ? 1 : (n_tokens < kPrefillChunk ? n_tokens : kPrefillChunk);
-  // units u with u us < L0 + T and u us + ul > L0
-  w.nu_touch = (int)ceil_div(w.T + m.ul, m.us) + 1;
-  const DecodeWs d = decode_ws_layout(m);
-  w.n_wg = (int)ceil_div((int64_t)m.k * (m.B / 32), kSparseWaves * kPrefillStepsPerWave);
-  w.part_stride = d.part_stride;
-  const int64_t nq = (int64_t)m.bh * w.T;
-  w.ustat = take((int64_t)m.bh * w.nu_touch * w.T * 2 * m.d * 4);
-  w.e_vals = take(nq * m.group * m.n_tiles * kTileBlocks * 4);
+  const int64_t row = (int64_t)m.bh * m.group * m.n_tiles * kTileBlocks * 4;  // e_vals per position
+  int64_t T = kPrefillScoreBytes / row;
+  T = T < kPrefillMinChunk ? kPrefillMinChunk : (T > kPrefillMaxChunk ? kPrefillMaxChunk : T);
+  w.T = (int)(n_tokens < 1 ? 1 : (n_tokens < T ? n_tokens : T));
+  w.part_stride = kPartHead + 2 * m.group * m.d;
+  const int64_t nq = (int64_t)m.bh * w.T, nb = (int64_t)m.bh * prefill_blocks(m, w.T);
+  w.ell_part = take(nq * (m.ul / m.us) * m.group * 8);
+  w.e_vals = take(row * w.T);
   w.tile_part = take(nq * m.n_tiles * m.group * 2 * 8);
   w.sel = take(nq * m.k * 4);
-  w.meta = take(nq * 4 * 4);
-  w.part = take(nq * w.n_wg * w.part_stride * 4);
-  w.obar = take(nq * m.group * m.d * 4);
-  w.zq = take(nq * m.group * 4);
+  w.near = take((1 + nq) * 4);
+  w.part_s = take(nb * m.d * m.d * 4);
+  w.part_z = take(nb * m.d * 4);
+  w.s_hi = take(nb * m.d * m.d * 2);
+  w.s_lo = take(nb * m.d * m.d * 2);
+  w.z_pre = take(nb * m.d * 4);
+  // records: T n_split(T) per (sequence, KV head), at most T times the largest
+  // split and at most T + kPrefillFill (positions per group) / bh (n_split <
+  // kPrefillFill / groups + 1, groups >= bh T / positions); none when no
+  // smaller chunk splits either
+  const int64_t qw = 4 * prefill_wave_positions(m.group);
+  const int64_t by_fill = w.T + ceil_div(kPrefillFill * qw, m.bh);
+  const int64_t by_split = (int64_t)w.T * kPrefillMaxSplit;
+  const bool splits = prefill_splits(m, 1) > 1;
+  w.part = take(splits ? (int64_t)m.bh * (by_fill < by_split ? by_fill : by_split) * w.part_stride * 4
+                       : 0);
   w.total = off;
   return w;
 }

@@ -144,6 +144,49 @@ struct SelectSmem {
   int32_t out[SPLA_MAX_TOP_K + 1];
 };
 
+// The kp-th largest of the keys held R per thread by the NT threads (0: not
+// a candidate), found digit by digit as in select_blocks: keys above gt are
+// taken and, of the keys equal to eqv, the first eq_need in thread order.
+// Fewer than kp candidates: every candidate (gt = 0). hist: 4096 words,
+// zeroed by the caller before a barrier.
+template <int NT, int R>
+__device__ __forceinline__ void radix_cut(const uint32_t (&key)[R], uint32_t kp, uint32_t* hist,
+                                          uint32_t& gt, uint32_t& eqv, uint32_t& eq_need) {
+  gt = 0xFFFFFFFFu;
+  eqv = 0u;
+  eq_need = 0u;
+  uint32_t prefix = 0u, need = kp;
+#pragma unroll
+  for (int rd = 0; rd < 3; ++rd) {
+    const int sh = 20 - 10 * rd;
+    const uint32_t msk = rd == 0 ? 0x7FFu : 0x3FFu;
+    uint32_t* H = hist + (rd == 0 ? 0 : 1024 + 1024 * rd);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const bool in = (key[r] != 0u) & ((rd == 0) | ((key[r] >> (sh + 10)) == prefix));
+      if (__ballot(in) != 0ull) atomicAdd(&H[(key[r] >> sh) & msk], in ? 1u : 0u);
+    }
+    __syncthreads();
+    const RadixPick p = rd == 0 ? radix_pick<32>(H, need) : radix_pick<16>(H, need);
+    if (rd == 0 && p.total < need) {
+      gt = 0u;
+      return;
+    }
+    need -= p.above;
+    prefix = (prefix << 10) | p.digit;
+    if (need == p.cnt) {
+      const uint32_t lo = prefix << sh;
+      gt = lo == 0u ? 0u : lo - 1u;
+      return;
+    }
+    if (rd == 2) {
+      gt = prefix;
+      eqv = prefix;
+      eq_need = need;
+    }
+  }
+}
+
 // The selection of sequence x KV head bh (length seq_len, clipped to the
 // capacity) by the NT threads of a workgroup, thread t owning blocks
 // t R .. t R + R - 1 (NT R >= blocks of the capacity). The length is an
@@ -163,13 +206,16 @@ struct SelectSmem {
 // at most eight heads and eight blocks per thread every head's masses load
 // in one batch, and a wavefront that takes a second head's tile partials
 // loads them with the first head's. GEX: the group is GMAX exactly.
+// near_span > 0: where the cutoff separates two scores closer than near_span
+// (relative), nothing is written and the result is true (in every thread);
+// otherwise it is false.
 template <int NT, int R, int SWN, bool CO, int SEL_OFF = 0, bool WIN = false,
           int GMAX = SPLA_MAX_GROUP, bool GEX = false>
-__device__ void select_blocks(const Dims& m, int bh, int seq_len,
+__device__ bool select_blocks(const Dims& m, int bh, int seq_len,
                               const float* __restrict__ e_vals,
                               const double* __restrict__ tile_part, SelectSmem<NT, SWN>& sm,
                               int32_t* sel, int32_t* meta4, int32_t* so,
-                              float* wsc = nullptr) {
+                              float* wsc = nullptr, float near_span = 0.f) {
   constexpr int NW = NT / 64;
   constexpr int HC0 = R <= 2 ? 16 / R : (R <= 8 ? 4 : 32 / R);
   constexpr int HC = (R <= 8 && GMAX <= 8 && GMAX > HC0) ? GMAX : HC0;  // heads per load batch
@@ -243,7 +289,7 @@ __device__ void select_blocks(const Dims& m, int bh, int seq_len,
       Mem<CO>::st(meta4 + 2, L);
       Mem<CO>::st(meta4 + 3, 0);
     }
-    return;
+    return false;
   }
   const int n_tu = ((WIN ? nu : nb) + kTileBlocks - 1) / kTileBlocks;  // unit tiles present
   for (int x = tid; x < 1024; x += NT) reinterpret_cast<uint4*>(hist)[x] = make_uint4(0u, 0u, 0u, 0u);
@@ -426,6 +472,33 @@ __device__ void select_blocks(const Dims& m, int bh, int seq_len,
     }
   }
 
+  if (near_span > 0.f && kp > 0) {  // uniform
+    // the smallest score taken and the largest one left out (keys are a
+    // score's bits + 1; a score is never negative)
+    float lo = INFINITY, hi = -1.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const bool in = (key[r] != 0u) & (key[r] > gt), tie = (eq_need > 0u) & (key[r] == eqv);
+      const float f = __uint_as_float(key[r] - 1u);
+      lo = fminf(lo, (in | tie) ? f : INFINITY);
+      hi = fmaxf(hi, (!in & (key[r] != 0u)) ? f : -1.f);
+    }
+    lo = -wave_max(-lo);
+    hi = wave_max(hi);
+    if (lane == 0) {
+      sm.bits[0][w] = __float_as_uint(lo);
+      sm.bits[1][w] = __float_as_uint(hi);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+      lo = fminf(lo, __uint_as_float(sm.bits[0][x]));
+      hi = fmaxf(hi, __uint_as_float(sm.bits[1][x]));
+    }
+    if (hi >= lo * (1.0f - near_span)) return true;
+    __syncthreads();  // bits is written again below
+  }
+
   // --- 4. ascending output. Each thread leaves one word of taken bits (keys
   // above the threshold, forced blocks) and one of tie bits (keys equal to
   // it) for its R blocks; wavefront 0 then reads them NT / 64 threads per
@@ -445,7 +518,7 @@ __device__ void select_blocks(const Dims& m, int bh, int seq_len,
   sm.bits[0][tid] = tkb;
   sm.bits[1][tid] = tqb;
   __syncthreads();
-  if (w != 0) return;
+  if (w != 0) return false;
   // lane l covers blocks l TPL R .. (l + 1) TPL R - 1 as LW words (thread
   // q of the lane at bit q R: R divides 32, so no thread straddles a word)
   constexpr int TPL = NT / 64;  // threads per lane
@@ -502,6 +575,7 @@ __device__ void select_blocks(const Dims& m, int bh, int seq_len,
     Mem<CO>::st(meta4 + 2, L);
     Mem<CO>::st(meta4 + 3, tot);
   }
+  return false;
 }
 
 // ------------------------------------------------------------------------
@@ -520,49 +594,6 @@ __device__ void select_blocks(const Dims& m, int bh, int seq_len,
 constexpr int kSliceThreads = 256;
 constexpr int kSliceR = kSliceBlocks / kSliceThreads;     // blocks per thread
 constexpr int kSliceTiles = kSliceBlocks / kTileBlocks;   // 16 statistics tiles
-
-// The kp-th largest of the keys held R per thread by the NT threads (0: not
-// a candidate), found digit by digit as in select_blocks: keys above gt are
-// taken and, of the keys equal to eqv, the first eq_need in thread order.
-// Fewer than kp candidates: every candidate (gt = 0). hist: 4096 words,
-// zeroed by the caller before a barrier.
-template <int NT, int R>
-__device__ __forceinline__ void radix_cut(const uint32_t (&key)[R], uint32_t kp, uint32_t* hist,
-                                          uint32_t& gt, uint32_t& eqv, uint32_t& eq_need) {
-  gt = 0xFFFFFFFFu;
-  eqv = 0u;
-  eq_need = 0u;
-  uint32_t prefix = 0u, need = kp;
-#pragma unroll
-  for (int rd = 0; rd < 3; ++rd) {
-    const int sh = 20 - 10 * rd;
-    const uint32_t msk = rd == 0 ? 0x7FFu : 0x3FFu;
-    uint32_t* H = hist + (rd == 0 ? 0 : 1024 + 1024 * rd);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const bool in = (key[r] != 0u) & ((rd == 0) | ((key[r] >> (sh + 10)) == prefix));
-      if (__ballot(in) != 0ull) atomicAdd(&H[(key[r] >> sh) & msk], in ? 1u : 0u);
-    }
-    __syncthreads();
-    const RadixPick p = rd == 0 ? radix_pick<32>(H, need) : radix_pick<16>(H, need);
-    if (rd == 0 && p.total < need) {
-      gt = 0u;
-      return;
-    }
-    need -= p.above;
-    prefix = (prefix << 10) | p.digit;
-    if (need == p.cnt) {
-      const uint32_t lo = prefix << sh;
-      gt = lo == 0u ? 0u : lo - 1u;
-      return;
-    }
-    if (rd == 2) {
-      gt = prefix;
-      eqv = prefix;
-      eq_need = need;
-    }
-  }
-}
 
 // Slice sl (blocks sl kSliceBlocks ..) of sequence x KV head bh: the
 // candidates' keys and ids, ascending by id, to ck / ci (k slots) and their

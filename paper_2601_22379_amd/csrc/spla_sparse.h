@@ -94,18 +94,11 @@ __device__ __forceinline__ void load_vec(const float* base, uint32_t off, float 
 // wavefront then merges two heads at once (groups of 5 or 6 heads; the
 // single-launch kernel and the separate merge use the same form, so their
 // outputs agree bit for bit).
-// ADD: the records carry no share of the global term (the chunked prefill
-// computes o_bar and <phi(q), z_bar> for every query in a kernel of its own);
-// obar_add (this query's G x D rows) and zq_add (its G values) are added to
-// the sums of the records' linear fields instead.
-template <typename T, int D, bool CO, bool ADD = false, bool HALF = false, int NP = 8>
+template <typename T, int D, bool CO, bool HALF = false, int NP = 8>
 __device__ __forceinline__ void merge_head(const Dims& m, float eps, uint32_t flags,
                                            const float* __restrict__ gamma, int all_sel, int L,
                                            const float* rec, int n_rec, int stride,
-                                           T* __restrict__ out, int bh, int g,
-                                           const float* __restrict__ obar_add = nullptr,
-                                           const float* __restrict__ zq_add = nullptr) {
-  static_assert(!(ADD && HALF), "one head per wavefront with ADD");
+                                           T* __restrict__ out, int bh, int g) {
   constexpr int E = D / 32;            // coordinates per lane
   // NP: record pairs (HALF: records) per load batch
   constexpr int HB = HALF ? 32 : 64;   // records per batch of headers
@@ -126,10 +119,6 @@ __device__ __forceinline__ void merge_head(const Dims& m, float eps, uint32_t fl
   float osp[E], ot[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) osp[e] = ot[e] = 0.f;
-  if constexpr (ADD) {  // once per coordinate: the halves are added at the end
-#pragma unroll
-    for (int e = 0; e < E; ++e) ot[e] = hf ? 0.f : obar_add[g * D + c0 + e];
-  }
   auto red_max = [](float v) { return HALF ? half_wave_max(v) : wave_max(v); };
   auto red_sum = [](float v) { return HALF ? half_wave_sum(v) : wave_sum(v); };
   for (int x0 = 0; x0 < n_rec; x0 += HB) {
@@ -198,7 +187,6 @@ __device__ __forceinline__ void merge_head(const Dims& m, float eps, uint32_t fl
       ot[e] += xor32(ot[e]);
     }
   }
-  if constexpr (ADD) zt += zq_add[g];
   float o[E];
   if (L == 0) {
 #pragma unroll
@@ -270,7 +258,7 @@ struct SparseRegs {
 
 // The loads of sparse_prologue: this lane's query elements (raw) and this
 // workgroup's rows of S_bar and z_bar (into r).
-template <int D, int GC, bool LIN = true>
+template <int D, int GC>
 __device__ __forceinline__ void sparse_prologue_load(const Dims& m, const bf16_t* __restrict__ q,
                                                      const float* __restrict__ S,
                                                      const float* __restrict__ zbar, int bh,
@@ -288,29 +276,20 @@ __device__ __forceinline__ void sparse_prologue_load(const Dims& m, const bf16_t
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) raw[ks] = *reinterpret_cast<const uint4*>(qrow + 32 * ks);
   lin_rows(D, x, n_wg, &r.row0, &r.nrows);
-  if constexpr (!LIN) {
+  // the first kSparsePre * 256 / D rows (sparse_linear reads any further
+  // ones itself); loads issued whether or not in range (from row 0 when
+  // not): no branch
+  const float* Sh = S + (int64_t)bh * D * D;
 #pragma unroll
-    for (int u = 0; u < kSparsePre; ++u) r.spre[u] = 0.f;
-    r.zbv = 0.f;
-    r.nrows = 0;
-  } else {
-    // the first kSparsePre * 256 / D rows (sparse_linear reads any further
-    // ones itself); loads issued whether or not in range (from row 0 when
-    // not): no branch
-    const float* Sh = S + (int64_t)bh * D * D;
-#pragma unroll
-    for (int u = 0; u < kSparsePre; ++u) {
-      const int e = tid + 256 * u;
-      const bool ok = e < r.nrows * D;
-      const float v = Sh[ok ? r.row0 * D + e : 0];
-      r.spre[u] = ok ? v : 0.f;
-    }
+  for (int u = 0; u < kSparsePre; ++u) {
+    const int e = tid + 256 * u;
+    const bool ok = e < r.nrows * D;
+    const float v = Sh[ok ? r.row0 * D + e : 0];
+    r.spre[u] = ok ? v : 0.f;
   }
-  if constexpr (LIN) {
-    const bool ok = tid < r.nrows;
-    const float v = zbar[(int64_t)bh * D + (ok ? r.row0 + tid : 0)];
-    r.zbv = ok ? v : 0.f;
-  }
+  const bool ok = tid < r.nrows;
+  const float v = zbar[(int64_t)bh * D + (ok ? r.row0 + tid : 0)];
+  r.zbv = ok ? v : 0.f;
 }
 
 // The arithmetic of the prologue, from the query elements raw.
@@ -387,31 +366,22 @@ __device__ __forceinline__ void sparse_prologue_finish(const Dims& m, const uint
 // are zero. The four lanes of a column (g = 0..3) hold all d coordinates of
 // its head, so the softmax of phi(q) needs only the two lane swaps. Also
 // issues the loads of this workgroup's rows of S_bar and z_bar (x of n_wg).
-// LIN = false: no share of the global term (no S_bar rows are loaded; ob and
-// zq stay zero), for the chunked prefill.
-template <int D, int GC, bool LIN = true>
+template <int D, int GC>
 __device__ __forceinline__ void sparse_prologue(const Dims& m, const bf16_t* __restrict__ q,
                                                 const float* __restrict__ S,
                                                 const float* __restrict__ zbar, int bh, int x,
                                                 int n_wg, SparseRegs& r, SparseSmem<D, GC>& sm) {
   uint4 raw[D / 32];
-  sparse_prologue_load<D, GC, LIN>(m, q, S, zbar, bh, x, n_wg, r, raw);
+  sparse_prologue_load<D, GC>(m, q, S, zbar, bh, x, n_wg, r, raw);
   sparse_prologue_finish<D, GC>(m, raw, sm);
 }
 
 // This workgroup's rows x of the global linear term (Eq. 15): ob and zq of r,
 // from the S_bar rows of r and phi(q) (LDS). Needs nothing from the
 // selection, so it runs while the workgroup would otherwise wait for it.
-template <int D, int GC, bool LIN = true>
+template <int D, int GC>
 __device__ __forceinline__ void sparse_linear(const Dims& m, const float* __restrict__ S, int bh,
                                               SparseRegs& r, SparseSmem<D, GC>& sm) {
-  if constexpr (!LIN) {
-    __syncthreads();  // the query operands and phi(q) are in LDS
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r.ob[i] = 0.f;
-    r.zq = 0.f;
-    return;
-  }
   constexpr int NO = (GC * D + 255) / 256;  // outputs (head, coordinate) per thread
   constexpr int RMAX = kSparsePre * 256 / D;  // rows held in LDS
   static_assert(NO <= 4, "ob holds four outputs");
@@ -577,8 +547,8 @@ struct SparseKV {
 // none; clipped to the last block) and its valid token count (0: nothing).
 template <int BLK>
 __device__ __forceinline__ int sparse_step_block(const Dims& m, int blk_sel, int& L, int x,
-                                                 int* n_valid, int ch_in = -1) {
-  const int ch = ch_in >= 0 ? ch_in : (x * kSparseWaves + (int)(threadIdx.x >> 6)) % (BLK / 32);
+                                                 int* n_valid) {
+  const int ch = (x * kSparseWaves + (int)(threadIdx.x >> 6)) % (BLK / 32);
   L = min(max(L, 0), m.cap);
   const int nb = (L + BLK - 1) / BLK;
   const int blk = blk_sel >= nb ? nb - 1 : blk_sel;
@@ -593,10 +563,10 @@ template <int D, int BLK>
 __device__ __forceinline__ void sparse_load(const Dims& m, const bf16_t* __restrict__ kc,
                                             const bf16_t* __restrict__ vc, int blk, int bh,
                                             int x, const int32_t* __restrict__ table,
-                                            SparseKV<D>& kv, int ch_in = -1) {
+                                            SparseKV<D>& kv) {
   constexpr int KS = D / 32, MT = D / 16;
   const int lane = threadIdx.x & 63;
-  const int ch = ch_in >= 0 ? ch_in : (x * kSparseWaves + (int)(threadIdx.x >> 6)) % (BLK / 32);
+  const int ch = (x * kSparseWaves + (int)(threadIdx.x >> 6)) % (BLK / 32);
   int64_t step0;
   if (table) {
     const int p = block_page(m, table, bh, blk);
@@ -617,9 +587,7 @@ __device__ __forceinline__ void sparse_load(const Dims& m, const bf16_t* __restr
 // The two products of one step (n_valid > 0): S = K [q | phi(q)]^T, the
 // step's softmax over the exact columns, and acc_o = V^T P; m_run / l_run get
 // the step's max and sum (exact columns) or the sum of the linear weights.
-// ONLINE: acc_o, m_run and l_run already hold earlier steps of this
-// wavefront; the exact columns are rescaled to the running max first.
-template <int D, int GC, bool ONLINE = false>
+template <int D, int GC>
 __device__ __forceinline__ void sparse_mma(float s, SparseKV<D>& kv, SparseSmem<D, GC>& sm,
                                            floatx4 (&acc_o)[D / 16], float& m_run,
                                            float& l_run) {
@@ -685,14 +653,6 @@ __device__ __forceinline__ void sparse_mma(float s, SparseKV<D>& kv, SparseSmem<
   }
   cmax = fmaxf(cmax, xor16(cmax));
   cmax = fmaxf(cmax, xor32(cmax));
-  float alpha = 1.f;  // ONLINE: the earlier steps' scale (exact columns)
-  if constexpr (ONLINE) {
-    if (exact_col) {
-      const float mn = fmaxf(m_run, cmax);
-      alpha = m_run == -INFINITY ? 0.f : __expf(m_run - mn);
-      cmax = mn;
-    }
-  }
   float psum = 0.f;
   bf16x8 bh8, bl8;
   float pv[8];
@@ -704,13 +664,7 @@ __device__ __forceinline__ void sparse_mma(float s, SparseKV<D>& kv, SparseSmem<
   split_bf16x8(pv, bh8, bl8);
   psum += xor16(psum);
   psum += xor32(psum);
-  if constexpr (ONLINE) {
-#pragma unroll
-    for (int t = 0; t < MT; ++t) acc_o[t] = acc_o[t] * alpha;
-    l_run = fmaf(l_run, alpha, psum);
-  } else {
-    l_run = psum;
-  }
+  l_run = psum;
   m_run = exact_col ? cmax : -INFINITY;
   if (n_valid < 32) {  // rows past the sequence end may hold anything: zero them
 #pragma unroll
@@ -726,15 +680,12 @@ __device__ __forceinline__ void sparse_mma(float s, SparseKV<D>& kv, SparseSmem<
   }
 }
 
-// Merges the four wavefronts' accumulators into the record of workgroup x:
-// row bh of the records, or rec_row (the chunked prefill keeps one row per
-// (sequence, KV head, position)).
+// Merges the four wavefronts' accumulators into the record of workgroup x.
 template <int D, bool CO, int GC>
 __device__ __forceinline__ void sparse_record(const Dims& m, const floatx4 (&acc_o)[D / 16],
                                               float m_run, float l_run, int bh, int x, int n_wg,
                                               const SparseRegs& r, SparseSmem<D, GC>& sm,
-                                              float* __restrict__ part, int stride,
-                                              int64_t rec_row) {
+                                              float* __restrict__ part, int stride) {
   constexpr int MT = D / 16;
   constexpr int NO = (GC * D + 255) / 256;  // outputs (head, coordinate) per thread
   const int G = m.group;
@@ -755,7 +706,7 @@ __device__ __forceinline__ void sparse_record(const Dims& m, const floatx4 (&acc
     sm.l[w][lane] = l_run;
   }
   __syncthreads();
-  float* rec = part + ((rec_row >= 0 ? rec_row : (int64_t)bh) * n_wg + x) * stride;
+  float* rec = part + ((int64_t)bh * n_wg + x) * stride;
 #pragma unroll
   for (int i = 0; i < NO; ++i) {
     const int e = tid + 256 * i;
@@ -812,8 +763,7 @@ __device__ __forceinline__ void sparse_body(const Dims& m, float s,
                                             int bh, int x, int n_wg, const SparseRegs& r,
                                             SparseSmem<D, GC>& sm, float* __restrict__ part,
                                             int stride,
-                                            const int32_t* __restrict__ table = nullptr,
-                                            int64_t rec_row = -1) {
+                                            const int32_t* __restrict__ table = nullptr) {
   constexpr int MT = D / 16;
   SparseKV<D> kv;
   const int blk = sparse_step_block<BLK>(m, blk_sel, L, x, &kv.n_valid);
@@ -828,44 +778,7 @@ __device__ __forceinline__ void sparse_body(const Dims& m, float s,
     sparse_load<D, BLK>(m, kc, vc, blk, bh, x, table, kv);
     sparse_mma<D, GC>(s, kv, sm, acc_o, m_run, l_run);
   }
-  sparse_record<D, CO, GC>(m, acc_o, m_run, l_run, bh, x, n_wg, r, sm, part, stride, rec_row);
-}
-
-// sparse_body with SPW consecutive 32-token steps per wavefront: step
-// (x kSparseWaves + w) SPW + j of the selection (B / 32 steps per selected
-// block, entries of sel_row), accumulated online, then one record per
-// workgroup (n_wg = k B / (32 kSparseWaves SPW) records per query).
-template <int D, int BLK, bool CO, int GC, int SPW>
-__device__ __forceinline__ void sparse_body_steps(const Dims& m, float s,
-                                                  const bf16_t* __restrict__ kc,
-                                                  const bf16_t* __restrict__ vc,
-                                                  const int32_t* __restrict__ sel_row, int L,
-                                                  int bh, int x, int n_wg, const SparseRegs& r,
-                                                  SparseSmem<D, GC>& sm, float* __restrict__ part,
-                                                  int stride,
-                                                  const int32_t* __restrict__ table,
-                                                  int64_t rec_row) {
-  constexpr int MT = D / 16, CPB = BLK / 32;
-  floatx4 acc_o[MT];
-#pragma unroll
-  for (int t = 0; t < MT; ++t) acc_o[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
-  const int g0 = (x * kSparseWaves + (int)(threadIdx.x >> 6)) * SPW;
-#pragma unroll
-  for (int j = 0; j < SPW; ++j) {
-    const int gs = g0 + j, e = gs / CPB, ch = gs % CPB;
-    const int v = e < m.k ? sel_row[e] : -1;
-    const int blk_sel = __builtin_amdgcn_readfirstlane(v);
-    SparseKV<D> kv;
-    int Lj = L;
-    const int blk = sparse_step_block<BLK>(m, blk_sel, Lj, x, &kv.n_valid, ch);
-    if (kv.n_valid > 0) {
-      sparse_load<D, BLK>(m, kc, vc, blk, bh, x, table, kv, ch);
-      if (j == 0) sparse_mma<D, GC>(s, kv, sm, acc_o, m_run, l_run);
-      else sparse_mma<D, GC, true>(s, kv, sm, acc_o, m_run, l_run);
-    }
-  }
-  sparse_record<D, CO, GC>(m, acc_o, m_run, l_run, bh, x, n_wg, r, sm, part, stride, rec_row);
+  sparse_record<D, CO, GC>(m, acc_o, m_run, l_run, bh, x, n_wg, r, sm, part, stride);
 }
 
 }  // namespace spla
