@@ -4,8 +4,9 @@
 // the heads scored first overlap the statistics stream of the others.
 //
 // One workgroup per item, in workgroup-index order:
-//   score items   kTilesPerItem 64-block statistics tiles of one (sequence,
-//                 KV head) (score_items), in (sequence, KV head) order. The
+//   score items   one 64-block statistics tile of one (sequence, KV head)
+//                 (score_items; two measured slower), in (sequence, KV head)
+//                 order. The
 //                 workgroup that finishes a head's last item runs the head's
 //                 selection (select_blocks), which publishes every selected
 //                 block as its own word (block + 2, never 0).
@@ -41,7 +42,6 @@
 namespace spla {
 
 constexpr int kSpinLimit = 1 << 20;  // polls of a wait (about a second)
-constexpr int kTilesPerItem = 1;  // statistics tiles per score item (two measured slower)
 
 struct FusedArgs {
   Dims m;
@@ -73,11 +73,86 @@ struct FusedArgs {
   int rot;      // the sparse items start with (sequence, KV head) rot (sparse_rotation)
   int stride;   // floats per record
   const int32_t* table;  // block table of a paged K/V pool, or NULL
-  // fused step: the token appended to each (sequence, KV head) and how many
-  // tokens each sequence received (0 at capacity), or NULL
+  // step: the token appended to each (sequence, KV head), or NULL, and what
+  // it changes
   const bf16_t* k_step;
   const bf16_t* v_step;
-  const int32_t* appended;
+  float* stats_w;
+  bf16_t* kc_w;
+  bf16_t* vc_w;
+  int32_t* lens_w;
+};
+
+// The gate of a score item (score_items): tiles past the sequence's end are not
+// scored; and the appended token of a step (spla_step), in the item whose tile
+// holds its block: thread j < d merges coordinate j of the key into the block's
+// mean and M2 (the arithmetic of the single-token append), writes them and the
+// key and value elements, and leaves the new statistics in LDS for the lanes
+// that score the block (apply). The rows go device-coherent: a sparse item of this
+// launch may read them, after the selection this item's arrival precedes.
+template <int BLK, bool STEP>
+struct ScoreGate {
+  static constexpr bool on = true, early = STEP;
+  static constexpr int D = 128;
+  const FusedArgs& a;
+  float (*s_new)[STEP ? D : 4];  // LDS: mean, M2
+  int bh, i;  // (sequence, KV head), tile
+  int len;    // seq_lens entry, as loaded (clipped where it is used: a use
+              // before the statistics loads would hold them up)
+
+  // lengths before and after the token
+  __device__ int before() const { return min(max(len, 0), a.m.cap); }
+  __device__ int length() const {
+    const int L0 = before();
+    return L0 + (STEP && L0 < a.m.cap ? 1 : 0);
+  }
+
+  // units of the tile, or the first tile of an empty sequence
+  __device__ bool live() const {
+    return i < max(1, ((length() + BLK - 1) / BLK + kTileBlocks - 1) / kTileBlocks);
+  }
+  // whether this item holds the token's block (uniform)
+  __device__ bool token() const {
+    return STEP && before() < a.m.cap && before() / BLK / kTileBlocks == i;
+  }
+  __device__ void load() const {
+    const int j = threadIdx.x;
+    if (!token() || j >= D) return;
+    const Dims& m = a.m;
+    const int L0 = before(), blk = L0 / BLK, na = L0 % BLK;
+    const bf16_t kv = a.k_step[(int64_t)bh * D + j], vv = a.v_step[(int64_t)bh * D + j];
+    int64_t slot = (int64_t)bh * m.nb_cap + blk;
+    if (a.table) {
+      const int p = block_page(m, a.table, bh, blk);
+      slot = p < 0 ? -1 : (int64_t)p * m.hkv + bh % m.hkv;
+      if (p < 0 && a.err_flags && j == 0) atomicOr(a.err_flags, (int)SPLA_DEVERR_PAGE);
+    }
+    if (slot >= 0) {
+      Mem<true>::st(&a.kc_w[k_off_slot(m, slot, na, j)].bits, kv.bits);
+      Mem<true>::st(&a.vc_w[v_off_slot(m, slot, na, j)].bits, vv.bits);
+    }
+    double mean = (double)bf16_to_f32(kv.bits), m2 = 0.0;
+    const int64_t o_mean = stats_off4(m, bh, blk, 0, j / 4) + (j & 3);
+    const int64_t o_m2 = stats_off4(m, bh, blk, 1, j / 4) + (j & 3);
+    if (na > 0) {
+      const double mean_a = a.stats[o_mean], m2_a = a.stats[o_m2];
+      const double n = (double)(na + 1), delta = mean - mean_a;
+      mean = mean_a + delta * (1 / n);
+      m2 = m2_a + delta * delta * ((double)na / n);
+    }
+    a.stats_w[o_mean] = s_new[0][j] = (float)mean;
+    a.stats_w[o_m2] = s_new[1][j] = (float)m2;
+  }
+  template <int NJ>
+  __device__ void apply(TileBuf<NJ>& buf, int bi, int qt) const {
+    if (!token() || bi != (before() / BLK) % kTileBlocks) return;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      buf.mu[j] = *reinterpret_cast<const float4*>(&s_new[0][4 * (qt * NJ + j)]);
+      // (first order: the second moments are re-read means)
+      buf.m2[j] = *reinterpret_cast<const float4*>(&s_new[a.first_order ? 0 : 1][4 * (qt * NJ + j)]);
+    }
+  }
 };
 
 
@@ -95,9 +170,16 @@ __device__ __forceinline__ void report_sync_error(const FusedArgs& a) {
 constexpr int kDecodeWaves = 3;
 
 // R: blocks per thread of the selection (256 R >= blocks per sequence).
-// STEP: the sparse items first apply the step's rank-one update (step_rank1).
+// STEP: a step's append and decode in one launch. The score item whose tile
+// holds the token's block appends the token's rows and statistics (ScoreGate),
+// the sparse items apply its rank-one update of S_bar (step_rank1, PRE entries
+// per thread), and the workgroup that merges a sequence's last head advances
+// the length: by then every score item of the sequence has counted itself in
+// and every sparse item of it has written its record, so all have read the
+// length before the token. (A launch of its own for the append cost 4.3 us
+// for one sequence of 8 heads, 7.7 us for 16.)
 // WAVES: waves per SIMD the kernel is built for (3 or 4).
-template <int G, int BLK, int R, bool STEP, int WAVES>
+template <int G, int BLK, int R, bool STEP, int WAVES, int PRE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES)))
 void decode_kernel(FusedArgs a) {
   constexpr int D = 128;
@@ -106,8 +188,9 @@ void decode_kernel(FusedArgs a) {
   __shared__ union {
     ScoreSmem<G> sc;
     SelectSmem<256, SWN> se;
-    SparseSmem<D, GC> sp;
+    SparseSmem<D, GC, PRE> sp;
   } sm;
+  __shared__ __align__(16) float s_new[STEP ? 2 : 1][STEP ? D : 4];
   __shared__ int s_flag;
   __shared__ int s_words[4];
   const Dims& m = a.m;
@@ -119,12 +202,19 @@ void decode_kernel(FusedArgs a) {
     // ---------------------------------------------------------- score item
     const int t = (int)blockIdx.x;
     const int bh = t / a.n_si, i = t % a.n_si;
-    const int L = a.seq_lens[bh / m.hkv];  // for the selection; loaded long before it is used
-    score_items<G, bf16_t, D, true, kTilesPerItem>(
-        m, a.stats, a.seq_lens, a.q, a.s_score, a.first_order,
-        bh * m.n_tiles + i * kTilesPerItem, a.e_vals, a.tile_part, sm.sc);
+    const ScoreGate<BLK, STEP> gate{a, s_new, bh, i, a.seq_lens[bh / m.hkv]};
+    const bool live =
+        score_items<G, bf16_t, D, true, 1>(m, a.stats, 0, a.q, a.s_score, a.first_order,
+                                           bh * m.n_tiles + i, a.e_vals, a.tile_part, sm.sc, gate);
+    // in a step every item counts itself in: the length may advance only
+    // after all of them have read it
+    if (!STEP && !live) return;
+    const int L = gate.length();
+    if (STEP && L == gate.before() && i == 0 && bh % m.hkv == 0 && tid == 0 && a.err_flags)
+      atomicOr(a.err_flags, (int)SPLA_DEVERR_CAPACITY);
     int32_t* done = sy + y.items_done + (int64_t)bh * kSyncLine;
-    if (!arrive_last(done, a.n_si, &s_flag)) return;
+    const int n_live = max(1, ((L + BLK - 1) / BLK + kTileBlocks - 1) / kTileBlocks);
+    if (!arrive_last(done, STEP ? a.n_si : n_live, &s_flag)) return;
     // the selection is on the path to the head's output: its wavefronts go
     // ahead of the score items that share their SIMDs
     __builtin_amdgcn_s_setprio(3);
@@ -163,13 +253,14 @@ void decode_kernel(FusedArgs a) {
   };
   uint4 cv = make_uint4(1u, 1u, 1u, 1u);
   if (poller) cv = Mem<true>::ld16(words, chunk);
-  const int L = min(max(a.seq_lens[bh / m.hkv], 0), m.cap);  // not produced in this launch
-  SparseRegs r;
-  sparse_prologue<D, GC>(m, a.q, a.S, a.zbar, bh, x, a.n_wg, r, sm.sp);
+  const int L0 = min(max(a.seq_lens[bh / m.hkv], 0), m.cap);
+  const int L = L0 + (STEP && L0 < m.cap ? 1 : 0);
+  SparseRegs<PRE> r;
+  sparse_prologue<D, GC, PRE>(m, a.q, a.S, a.zbar, bh, x, a.n_wg, r, sm.sp);
   if constexpr (STEP)
-    step_rank1<D>(m, a.k_step, a.v_step, a.appended, const_cast<float*>(a.S),
+    step_rank1<D, PRE>(m, a.k_step, a.v_step, L - L0, const_cast<float*>(a.S),
                   const_cast<float*>(a.zbar), bh, r);
-  sparse_linear<D, GC>(m, a.S, bh, r, sm.sp);
+  sparse_linear<D, GC, PRE>(m, a.S, bh, r, sm.sp);
   if (poller && !ready(cv)) {
     // three polls in flight: each turn issues one and takes the oldest, so
     // a published word is seen about one memory round trip after it lands
@@ -206,7 +297,7 @@ void decode_kernel(FusedArgs a) {
   const int step = sparse_step_entry<BLK>(x);
   const int v = step < m.k ? s_words[tid >> 6] : 1;  // 0 only after a wait that gave up
   const int blk_sel = __builtin_amdgcn_readfirstlane(v) - 2;
-  sparse_body<D, BLK, true, GC>(m, a.s, a.kc, a.vc, blk_sel, L, bh, x, a.n_wg, r, sm.sp, a.part,
+  sparse_body<D, BLK, true, GC, PRE>(m, a.s, a.kc, a.vc, blk_sel, L, bh, x, a.n_wg, r, sm.sp, a.part,
                                 a.stride, a.table);
   if (poller) {  // the workgroup's entries, read by it only
 #pragma unroll
@@ -228,7 +319,17 @@ void decode_kernel(FusedArgs a) {
       merge_head<bf16_t, D, true>(m, a.eps, a.flags, a.gamma, all_sel, L, rec, a.n_wg, a.stride,
                                   a.out, bh, g);
   }
-  if (tid == 0) store_agent(recs, 0);  // last, as for the item counter
+  if (tid == 0) {
+    store_agent(recs, 0);  // last, as for the item counter
+    if constexpr (STEP) {
+      const int b = bh / m.hkv;
+      int32_t* merged = sy + y.recs_done + (int64_t)b * m.hkv * kSyncLine + 1;
+      if (atomic_add_agent(merged, 1) == m.hkv - 1) {
+        if (L > L0) a.lens_w[b] = L;
+        store_agent(merged, 0);
+      }
+    }
+  }
 }
 
 // The (sequence, KV head) the sparse items start with: the heads whose
@@ -248,18 +349,15 @@ template <int G, int BLK, int R>
 static void decode_gbr(const FusedArgs& a0, hipStream_t st) {
   const int grid = a0.m.bh * (a0.n_si + a0.n_wg);
   const int cus = compute_units();  // one workgroup per wave of each SIMD
-  const bool four = !a0.appended && grid > kDecodeWaves * cus && grid <= 4 * cus;
+  const bool step = a0.k_step != nullptr;
+  const bool four = !step && grid > kDecodeWaves * cus && grid <= 4 * cus;
   FusedArgs a = a0;
   a.rot = sparse_rotation(a, (four ? 4 : kDecodeWaves) * cus);
-  if (a.appended)
-    hipLaunchKernelGGL((decode_kernel<G, BLK, R, true, kDecodeWaves>), dim3((unsigned)grid),
-                       dim3(256), 0, st, a);
-  else if (four)
-    hipLaunchKernelGGL((decode_kernel<G, BLK, R, false, 4>), dim3((unsigned)grid), dim3(256), 0,
-                       st, a);
-  else
-    hipLaunchKernelGGL((decode_kernel<G, BLK, R, false, kDecodeWaves>), dim3((unsigned)grid),
-                       dim3(256), 0, st, a);
+  auto kern = four ? decode_kernel<G, BLK, R, false, 4, kSparsePre>
+              : !step ? decode_kernel<G, BLK, R, false, kDecodeWaves, kSparsePre>
+              : step_pre(a.m) <= kSparsePre ? decode_kernel<G, BLK, R, true, kDecodeWaves, kSparsePre>
+                                            : decode_kernel<G, BLK, R, true, kDecodeWaves, kStepPre>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, st, a);
 }
 
 template <int G, int R>
@@ -304,13 +402,16 @@ static hipError_t decode_fused(const Dims& m, const spla_config& cfg, const spla
   a.eps = cfg.rms_eps;
   a.flags = cfg.flags;
   a.first_order = (cfg.flags & SPLA_FLAG_FIRST_ORDER) != 0;
-  a.n_si = (int)ceil_div(m.n_tiles, kTilesPerItem);
+  a.n_si = m.n_tiles;
   a.n_wg = ws.n_wg;
   a.stride = ws.part_stride;
   a.table = m.pages > 0 ? c.block_table : nullptr;
   a.k_step = (const bf16_t*)k_step;
   a.v_step = (const bf16_t*)v_step;
-  a.appended = k_step ? (const int32_t*)(base + ws.appended) : nullptr;
+  a.stats_w = c.blk_stats;
+  a.kc_w = (bf16_t*)c.k_cache;
+  a.vc_w = (bf16_t*)c.v_cache;
+  a.lens_w = c.seq_lens;
   switch (m.group) {
     case 1: decode_g<1>(a, st); break;
     case 2: decode_g<2>(a, st); break;

@@ -25,7 +25,7 @@ __global__ __launch_bounds__(256) void score_kernel(
   // selection reads the tiles that hold units only
   const int L = min(max(seq_lens[t / m.n_tiles / m.hkv], 0), m.cap);
   if ((t % m.n_tiles) * kTileBlocks * m.us >= L) return;
-  score_items<G, T, D, false, NT>(m, stats, seq_lens, q, s, first_order, t, e_vals, tile_part,
+  score_items<G, T, D, false, NT>(m, stats, L, q, s, first_order, t, e_vals, tile_part,
                                   sm);
 }
 
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void score_select_kernel(
   // a tile wholly past the sequence end is neither read nor scored, but
   // still counts itself in
   if (tile * kTileBlocks * m.us < L)
-    score_items<G, T, D, true, 1>(m, stats, seq_lens, q, s, first_order, t, e_vals, tile_part,
+    score_items<G, T, D, true, 1>(m, stats, L, q, s, first_order, t, e_vals, tile_part,
                                   sm.sc);
   int32_t* c = ctr + (int64_t)bh * kSyncLine;
   if (!arrive_last(c, m.n_tiles, &s_flag)) return;

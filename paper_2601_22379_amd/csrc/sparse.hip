@@ -295,7 +295,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
 // workgroup's rows of S_bar (step_rank1), as the single-launch step does.
 // GC: accumulator columns per kind (>= G). The selection's LDS (R > 0) lies
 // over the accumulators, which sparse_body writes only after the selection.
-template <int D, int BLK, int R, int GC, bool STEP>
+template <int D, int BLK, int R, int GC, bool STEP, int PRE = kSparsePre>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GC <= 4 ? 3 : 2)))
 void sparse_mfma_kernel(
     Dims m, float s, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
@@ -307,7 +307,7 @@ void sparse_mfma_kernel(
     const bf16_t* __restrict__ k_step = nullptr, const bf16_t* __restrict__ v_step = nullptr,
     const int32_t* __restrict__ appended = nullptr) {
   constexpr int SWN = R > 0 ? kTileBlocks * 8 : 4;  // tile weights: <= 64 tiles x 8 heads
-  using SpSm = SparseSmem<D, GC>;
+  using SpSm = SparseSmem<D, GC, PRE>;
   using SeSm = SelectSmem<256, SWN>;
   constexpr size_t kLds = R > 0 && SpSm::kOverlay + sizeof(SeSm) > sizeof(SpSm)
                               ? SpSm::kOverlay + sizeof(SeSm) : sizeof(SpSm);
@@ -319,7 +319,7 @@ void sparse_mfma_kernel(
   __shared__ int32_t s_meta[4];
   const int bh = blockIdx.y;
   const int x = (int)blockIdx.x;
-  SparseRegs r;
+  SparseRegs<PRE> r;
   if constexpr (R == 0) {
     // the selection is known at the start: the step's keys and values are
     // loaded first, behind only the query and S_bar loads, so that their
@@ -328,32 +328,32 @@ void sparse_mfma_kernel(
     const int blk_sel = e < m.k ? sel[(int64_t)bh * m.k + e] : -1;
     int L = meta[bh * 4 + 2];
     uint4 raw[D / 32];
-    sparse_prologue_load<D, GC>(m, q, S, zbar, bh, x, (int)gridDim.x, r, raw);
+    sparse_prologue_load<D, GC, PRE>(m, q, S, zbar, bh, x, (int)gridDim.x, r, raw);
     StepIn<D> sin;
-    if constexpr (STEP) step_load<D>(m, k_step, v_step, appended, bh, sin);
+    if constexpr (STEP) step_load<D>(m, k_step, v_step, appended[bh / m.hkv], bh, sin);
     SparseKV<D> kv;
     const int blk = sparse_step_block<BLK>(m, blk_sel, L, x, &kv.n_valid);
     sparse_load<D, BLK>(m, kc, vc, blk < 0 ? 0 : blk, bh, x, table, kv);
-    sparse_prologue_finish<D, GC>(m, raw, sm);
-    if constexpr (STEP) step_apply<D>(m, sin, S, zbar, bh, r);
-    sparse_linear<D, GC>(m, S, bh, r, sm);
+    sparse_prologue_finish<D, GC, PRE>(m, raw, sm);
+    if constexpr (STEP) step_apply<D, PRE>(m, sin, S, zbar, bh, r);
+    sparse_linear<D, GC, PRE>(m, S, bh, r, sm);
     floatx4 acc_o[D / 16];
 #pragma unroll
     for (int t = 0; t < D / 16; ++t) acc_o[t] = floatx4{0.f, 0.f, 0.f, 0.f};
     float m_run = -INFINITY, l_run = 0.f;
-    if (kv.n_valid > 0) sparse_mma<D, GC>(s, kv, sm, acc_o, m_run, l_run);
-    sparse_record<D, false, GC>(m, acc_o, m_run, l_run, bh, x, (int)gridDim.x, r, sm, part,
+    if (kv.n_valid > 0) sparse_mma<D, GC, PRE>(s, kv, sm, acc_o, m_run, l_run);
+    sparse_record<D, false, GC, PRE>(m, acc_o, m_run, l_run, bh, x, (int)gridDim.x, r, sm, part,
                                 stride);
   } else {  // every workgroup makes its head's selection itself
-    sparse_prologue<D, GC>(m, q, S, zbar, bh, x, (int)gridDim.x, r, sm);
-    sparse_linear<D, GC>(m, S, bh, r, sm);
+    sparse_prologue<D, GC, PRE>(m, q, S, zbar, bh, x, (int)gridDim.x, r, sm);
+    sparse_linear<D, GC, PRE>(m, S, bh, r, sm);
     select_blocks<256, R, SWN, false, 0, false, GC>(
         m, bh, seq_lens[bh / m.hkv], e_vals, tile_part, ssm, s_sel, s_meta,
         x == 0 && sel_out ? sel_out + (int64_t)bh * m.k : nullptr);
     __syncthreads();
     if (x == 0 && threadIdx.x < 4) meta[bh * 4 + threadIdx.x] = s_meta[threadIdx.x];
     const int e = sparse_step_entry<BLK>(x);
-    sparse_body<D, BLK, false, GC>(m, s, kc, vc, e < m.k ? s_sel[e] : -1, s_meta[2], bh, x,
+    sparse_body<D, BLK, false, GC, PRE>(m, s, kc, vc, e < m.k ? s_sel[e] : -1, s_meta[2], bh, x,
                                    (int)gridDim.x, r, sm, part, stride, table);
   }
 }
@@ -385,12 +385,12 @@ static int sparse_select_r(const Dims& m, bool step) {
 
 bool sparse_selects(const Dims& m, bool step) { return sparse_select_r(m, step) > 0; }
 
-template <int D, int BLK, int R, bool STEP>
+template <int D, int BLK, int R, bool STEP, int PRE = kSparsePre>
 static void mfma_dbr(const Dims& m, float s, const spla_cache& c, const void* q,
                      int32_t* sel_out, const DecodeWs& ws, char* base, hipStream_t st,
                      const void* k_step, const void* v_step) {
-  auto kern = m.group <= 4 ? sparse_mfma_kernel<D, BLK, R, 4, STEP>
-                           : sparse_mfma_kernel<D, BLK, R, 8, STEP>;
+  auto kern = m.group <= 4 ? sparse_mfma_kernel<D, BLK, R, 4, STEP, PRE>
+                           : sparse_mfma_kernel<D, BLK, R, 8, STEP, PRE>;
   hipLaunchKernelGGL(kern, dim3(ws.n_wg, m.bh), dim3(256), 0, st,
                      m, s, (const bf16_t*)c.k_cache, (const bf16_t*)c.v_cache, (const bf16_t*)q,
                      c.lin_state, c.lin_norm, (const int32_t*)(base + ws.sel),
@@ -406,7 +406,10 @@ static void mfma_db(const Dims& m, float s, const spla_cache& c, const void* q, 
                     const DecodeWs& ws, char* base, hipStream_t st, const void* k_step,
                     const void* v_step) {
   if (k_step) {
-    mfma_dbr<D, BLK, 0, true>(m, s, c, q, sel_out, ws, base, st, k_step, v_step);
+    if (step_pre(m) <= kSparsePre)
+      mfma_dbr<D, BLK, 0, true>(m, s, c, q, sel_out, ws, base, st, k_step, v_step);
+    else
+      mfma_dbr<D, BLK, 0, true, kStepPre>(m, s, c, q, sel_out, ws, base, st, k_step, v_step);
     return;
   }
   switch (sparse_select_r(m, false)) {

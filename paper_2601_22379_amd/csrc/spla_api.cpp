@@ -61,8 +61,9 @@ struct PhaseMark {
   } while (0)
 
 // k_step, v_step (or NULL): a step's token whose rank-one update of S_bar the
-// decode's sparse pass applies (step_fusable shapes, rows and statistics
-// already appended, ws.appended written by the finish kernel).
+// decode's sparse pass applies (step_fusable shapes); the single launch also
+// appends its rows and statistics, before the separate launches they are
+// appended already and ws.appended holds the tokens each sequence received.
 int32_t run_decode(const spla_config* cfg, const spla_cache* cache, const void* q,
                    const float* w, void* out, int32_t* sel_idx, void* ws, size_t ws_bytes,
                    const spla_events* ev, hipStream_t st, const void* k_step = nullptr,
@@ -200,12 +201,14 @@ extern "C" int32_t spla_step_ex(const spla_config* cfg, const spla_cache* cache,
   char* base = static_cast<char*>(ws);
   int32_t* fin = reinterpret_cast<int32_t*>(base + L.sync) + spla::sync_layout(m).items_done;
   if (spla::step_fusable(m)) {
-    // the token's rows and statistics first; its rank-one update of S_bar is
-    // applied by the decode's sparse pass to the rows it reads anyway
+    // the token's rows and statistics first (in one launch with the decode
+    // where that is one); its rank-one update of S_bar is applied by the
+    // decode's sparse pass to the rows it reads anyway
     {
       PhaseMark pm(ev, st, SPLA_PHASE_APPEND);
-      SPLA_TRY(spla::launch_append_one(m, *cache, k_new, v_new, st, false, fin,
-                                       reinterpret_cast<int32_t*>(base + L.appended)));
+      if (!spla::use_fused_decode(m) || (cfg->flags & SPLA_FLAG_SEPARATE_KERNELS))
+        SPLA_TRY(spla::launch_append_one(m, *cache, k_new, v_new, st, false, fin,
+                                         reinterpret_cast<int32_t*>(base + L.appended)));
     }
     return run_decode(cfg, cache, q, w, out, sel_idx, ws, ws_bytes, ev, st, k_new, v_new);
   }

@@ -100,11 +100,10 @@ hipError_t launch_decode_fused(const Dims& m, const spla_config& cfg, const spla
                                const void* q, const float* rms_weight, void* out,
                                int32_t* sel_out, const DecodeWs& ws, char* wsbase,
                                hipStream_t st);
-// The single-launch decode of a step whose token rows and statistics are
-// already appended (launch_append_one without rank1, then launch_append_finish
-// with ws.appended; step_fusable shapes): its sparse items add phi(k) v^T of
-// the token to the rows of S_bar (and z_bar) they read, use them, and write
-// them back, for each sequence that received the token.
+// A step in one launch (step_fusable shapes): the token's rows and statistics
+// are appended by the score items that hold its block, its rank-one update of
+// S_bar and z_bar is applied by the sparse items to the rows they read, and
+// the lengths advance at the end.
 hipError_t launch_decode_fused_step(const Dims& m, const spla_config& cfg, const spla_cache& c,
                                     const void* k_new, const void* v_new, const void* q,
                                     const float* rms_weight, void* out, int32_t* sel_out,

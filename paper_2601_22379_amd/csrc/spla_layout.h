@@ -118,6 +118,7 @@ SPLA_HD int64_t stats_off4(const Dims& m, int64_t bh, int64_t blk, int part, int
 constexpr int kPartHead = 48;     // per-record header: m[16], l[16], zw[16]
 constexpr int kSparseWaves = 4;   // waves per sparse workgroup
 constexpr int kSparsePre = 4;     // S_bar entries per thread a sparse workgroup holds
+constexpr int kStepPre = 8;       // ... in a step, where it has more rows (step_pre)
 
 struct DecodeWs {
   int64_t e_vals;     // f32 [bh][G][n_tiles*64]   exp(ell - tile max), per unit
@@ -165,7 +166,8 @@ constexpr int kSyncLine = 32;  // int32 words per line
 struct SyncLayout {
   int64_t err;         // error word (bad waits)
   int64_t items_done;  // [bh], line stride: score items finished
-  int64_t recs_done;   // [bh], line stride: sparse records written
+  int64_t recs_done;   // [bh], line stride: sparse records written; word 1 of the line of a
+                       //   sequence's first head: heads of the sequence merged (a step)
   int64_t sel_ready;   // [bh][k]: selected block + 2 (1: none), 0 until the selection
                        //   of that (sequence, KV head) is published
   int64_t words;
@@ -214,12 +216,14 @@ SPLA_HD DecodeWs decode_ws_layout(const Dims& m) {
 
 // spla_step folds the token's rank-one update of S_bar into the rows of
 // S_bar the matrix-core sparse pass reads (for o_bar) when every sparse
-// workgroup holds all its rows in registers.
-SPLA_HD bool step_fusable(const Dims& m) {
-  if (!use_mfma_sparse(m)) return false;
+// workgroup holds all its rows in registers: step_pre entries per thread, four
+// with 16 or more workgroups per head (d = 128), eight with 8 (k = 16 blocks of
+// 64; a separate update there cost 7.7 us for 128 heads).
+SPLA_HD int step_pre(const Dims& m) {
   const DecodeWs ws = decode_ws_layout(m);
-  return ceil_div(m.d, ws.n_wg) * m.d <= kSparsePre * 256;
+  return (int)ceil_div(ceil_div(m.d, ws.n_wg) * m.d, 256);
 }
+SPLA_HD bool step_fusable(const Dims& m) { return use_mfma_sparse(m) && step_pre(m) <= kStepPre; }
 
 // ---- chunked prefill workspace ------------------------------------------------
 // Positions per chunk: as many as keep the block masses of the chunk's queries

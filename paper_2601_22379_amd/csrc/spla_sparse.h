@@ -232,12 +232,12 @@ SPLA_HD bool merge_halves(int G) { return G > 4 && G <= kFusedMaxGroup; }
 // linear columns GC .. 2 GC-1), phi(q) and this workgroup's rows of S_bar.
 // The accumulators come last and are written only at the end of sparse_body,
 // so a kernel may lay other LDS over them until then (kOverlay).
-template <int D, int GC>
+template <int D, int GC, int PRE = kSparsePre>
 struct SparseSmem {
   uint4 qops[3][D / 32][64];
   float m[kSparseWaves][16], l[kSparseWaves][16];
   float phq[GC][D];
-  float S[kSparsePre * 256];
+  float S[PRE * 256];
   float zb[D];
   float o[kSparseWaves][D][2 * GC + 1];
   static constexpr size_t kOverlay = sizeof(qops) + sizeof(m) + sizeof(l) + sizeof(phq) +
@@ -248,8 +248,9 @@ struct SparseSmem {
 // of S_bar and z_bar (the query operands go to LDS), then its share of
 // phi(q) S_bar (ob: output e = tid + 256 i is head e / D, coordinate e % D)
 // and of <phi(q), z_bar> (zq, thread g < G for head g).
+template <int PRE = kSparsePre>
 struct SparseRegs {
-  float spre[kSparsePre];
+  float spre[PRE];
   float zbv;
   int row0, nrows;
   float ob[4];
@@ -258,11 +259,11 @@ struct SparseRegs {
 
 // The loads of sparse_prologue: this lane's query elements (raw) and this
 // workgroup's rows of S_bar and z_bar (into r).
-template <int D, int GC>
+template <int D, int GC, int PRE>
 __device__ __forceinline__ void sparse_prologue_load(const Dims& m, const bf16_t* __restrict__ q,
                                                      const float* __restrict__ S,
                                                      const float* __restrict__ zbar, int bh,
-                                                     int x, int n_wg, SparseRegs& r,
+                                                     int x, int n_wg, SparseRegs<PRE>& r,
                                                      uint4 (&raw)[D / 32]) {
   constexpr int KS = D / 32;
   const int b = bh / m.hkv, h = bh % m.hkv;
@@ -276,12 +277,12 @@ __device__ __forceinline__ void sparse_prologue_load(const Dims& m, const bf16_t
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) raw[ks] = *reinterpret_cast<const uint4*>(qrow + 32 * ks);
   lin_rows(D, x, n_wg, &r.row0, &r.nrows);
-  // the first kSparsePre * 256 / D rows (sparse_linear reads any further
+  // the first PRE * 256 / D rows (sparse_linear reads any further
   // ones itself); loads issued whether or not in range (from row 0 when
   // not): no branch
   const float* Sh = S + (int64_t)bh * D * D;
 #pragma unroll
-  for (int u = 0; u < kSparsePre; ++u) {
+  for (int u = 0; u < PRE; ++u) {
     const int e = tid + 256 * u;
     const bool ok = e < r.nrows * D;
     const float v = Sh[ok ? r.row0 * D + e : 0];
@@ -293,9 +294,9 @@ __device__ __forceinline__ void sparse_prologue_load(const Dims& m, const bf16_t
 }
 
 // The arithmetic of the prologue, from the query elements raw.
-template <int D, int GC>
+template <int D, int GC, int PRE>
 __device__ __forceinline__ void sparse_prologue_finish(const Dims& m, const uint4 (&raw)[D / 32],
-                                                       SparseSmem<D, GC>& sm) {
+                                                       SparseSmem<D, GC, PRE>& sm) {
   constexpr int KS = D / 32;
   const int G = m.group;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -366,29 +367,30 @@ __device__ __forceinline__ void sparse_prologue_finish(const Dims& m, const uint
 // are zero. The four lanes of a column (g = 0..3) hold all d coordinates of
 // its head, so the softmax of phi(q) needs only the two lane swaps. Also
 // issues the loads of this workgroup's rows of S_bar and z_bar (x of n_wg).
-template <int D, int GC>
+template <int D, int GC, int PRE>
 __device__ __forceinline__ void sparse_prologue(const Dims& m, const bf16_t* __restrict__ q,
                                                 const float* __restrict__ S,
                                                 const float* __restrict__ zbar, int bh, int x,
-                                                int n_wg, SparseRegs& r, SparseSmem<D, GC>& sm) {
+                                                int n_wg, SparseRegs<PRE>& r,
+                                                SparseSmem<D, GC, PRE>& sm) {
   uint4 raw[D / 32];
-  sparse_prologue_load<D, GC>(m, q, S, zbar, bh, x, n_wg, r, raw);
-  sparse_prologue_finish<D, GC>(m, raw, sm);
+  sparse_prologue_load<D, GC, PRE>(m, q, S, zbar, bh, x, n_wg, r, raw);
+  sparse_prologue_finish<D, GC, PRE>(m, raw, sm);
 }
 
 // This workgroup's rows x of the global linear term (Eq. 15): ob and zq of r,
 // from the S_bar rows of r and phi(q) (LDS). Needs nothing from the
 // selection, so it runs while the workgroup would otherwise wait for it.
-template <int D, int GC>
+template <int D, int GC, int PRE>
 __device__ __forceinline__ void sparse_linear(const Dims& m, const float* __restrict__ S, int bh,
-                                              SparseRegs& r, SparseSmem<D, GC>& sm) {
+                                              SparseRegs<PRE>& r, SparseSmem<D, GC, PRE>& sm) {
   constexpr int NO = (GC * D + 255) / 256;  // outputs (head, coordinate) per thread
-  constexpr int RMAX = kSparsePre * 256 / D;  // rows held in LDS
+  constexpr int RMAX = PRE * 256 / D;  // rows held in LDS
   static_assert(NO <= 4, "ob holds four outputs");
   const int G = m.group, tid = threadIdx.x;
   const int row0 = r.row0, nrows = r.nrows;
 #pragma unroll
-  for (int u = 0; u < kSparsePre; ++u) sm.S[tid + 256 * u] = r.spre[u];
+  for (int u = 0; u < PRE; ++u) sm.S[tid + 256 * u] = r.spre[u];
   if (tid < D) sm.zb[tid] = r.zbv;
   __syncthreads();  // the query operands, phi(q) and the S_bar rows are in LDS
   // the first RMAX rows from LDS (rows past nrows are zero there; their
@@ -450,19 +452,18 @@ struct StepIn {
 template <int D>
 __device__ __forceinline__ void step_load(const Dims& m, const bf16_t* __restrict__ k_step,
                                           const bf16_t* __restrict__ v_step,
-                                          const int32_t* __restrict__ appended, int bh,
-                                          StepIn<D>& in) {
+                                          int appended, int bh, StepIn<D>& in) {
   const int tid = threadIdx.x, lane = tid & 63;
-  in.app = appended[bh / m.hkv];
+  in.app = appended;
 #pragma unroll
   for (int e = 0; e < D / 64; ++e)
     in.x[e] = bf16_to_f32(k_step[(int64_t)bh * D + lane + 64 * e].bits);
   in.vc = bf16_to_f32(v_step[(int64_t)bh * D + tid % D].bits);
 }
 
-template <int D>
+template <int D, int PRE>
 __device__ __forceinline__ void step_apply(const Dims& m, StepIn<D>& in, float* S, float* zbar,
-                                           int bh, SparseRegs& r) {
+                                           int bh, SparseRegs<PRE>& r) {
   const int tid = threadIdx.x;
   if (in.app <= 0) return;  // uniform over the workgroup
   float mx = -INFINITY;
@@ -481,7 +482,7 @@ __device__ __forceinline__ void step_apply(const Dims& m, StepIn<D>& in, float* 
   for (int e = 0; e < D / 64; ++e) ph[e] = in.x[e] / sum;
   float* Sh = S + (int64_t)bh * D * D;
 #pragma unroll
-  for (int u = 0; u < kSparsePre; ++u) {
+  for (int u = 0; u < PRE; ++u) {
     const int e = tid + 256 * u;
     const int row = r.row0 + e / D;  // uniform over the wavefront
     const float pr = lane_f32(ph[(row % D) / 64], row % 64);
@@ -502,14 +503,14 @@ __device__ __forceinline__ void step_apply(const Dims& m, StepIn<D>& in, float* 
   }
 }
 
-template <int D>
+template <int D, int PRE>
 __device__ __forceinline__ void step_rank1(const Dims& m, const bf16_t* __restrict__ k_step,
                                            const bf16_t* __restrict__ v_step,
-                                           const int32_t* __restrict__ appended, float* S,
-                                           float* zbar, int bh, SparseRegs& r) {
+                                           int appended, float* S, float* zbar, int bh,
+                                           SparseRegs<PRE>& r) {
   StepIn<D> in;
   step_load<D>(m, k_step, v_step, appended, bh, in);
-  step_apply<D>(m, in, S, zbar, bh, r);
+  step_apply<D, PRE>(m, in, S, zbar, bh, r);
 }
 
 // Selected block of this wavefront's step: entry p of the selection, where
@@ -587,8 +588,8 @@ __device__ __forceinline__ void sparse_load(const Dims& m, const bf16_t* __restr
 // The two products of one step (n_valid > 0): S = K [q | phi(q)]^T, the
 // step's softmax over the exact columns, and acc_o = V^T P; m_run / l_run get
 // the step's max and sum (exact columns) or the sum of the linear weights.
-template <int D, int GC>
-__device__ __forceinline__ void sparse_mma(float s, SparseKV<D>& kv, SparseSmem<D, GC>& sm,
+template <int D, int GC, int PRE>
+__device__ __forceinline__ void sparse_mma(float s, SparseKV<D>& kv, SparseSmem<D, GC, PRE>& sm,
                                            floatx4 (&acc_o)[D / 16], float& m_run,
                                            float& l_run) {
   constexpr int KS = D / 32;     // k-steps of the first product
@@ -681,10 +682,11 @@ __device__ __forceinline__ void sparse_mma(float s, SparseKV<D>& kv, SparseSmem<
 }
 
 // Merges the four wavefronts' accumulators into the record of workgroup x.
-template <int D, bool CO, int GC>
+template <int D, bool CO, int GC, int PRE>
 __device__ __forceinline__ void sparse_record(const Dims& m, const floatx4 (&acc_o)[D / 16],
                                               float m_run, float l_run, int bh, int x, int n_wg,
-                                              const SparseRegs& r, SparseSmem<D, GC>& sm,
+                                              const SparseRegs<PRE>& r,
+                                              SparseSmem<D, GC, PRE>& sm,
                                               float* __restrict__ part, int stride) {
   constexpr int MT = D / 16;
   constexpr int NO = (GC * D + 255) / 256;  // outputs (head, coordinate) per thread
@@ -755,13 +757,13 @@ __device__ __forceinline__ void sparse_record(const Dims& m, const floatx4 (&acc
 // as bf16 hi + lo pairs (about 16 mantissa bits); accumulation is fp32. CO:
 // the record is written with Mem<true> (merged by another workgroup of the
 // same launch).
-template <int D, int BLK, bool CO, int GC>
+template <int D, int BLK, bool CO, int GC, int PRE>
 __device__ __forceinline__ void sparse_body(const Dims& m, float s,
                                             const bf16_t* __restrict__ kc,
                                             const bf16_t* __restrict__ vc,
                                             int blk_sel, int L,
-                                            int bh, int x, int n_wg, const SparseRegs& r,
-                                            SparseSmem<D, GC>& sm, float* __restrict__ part,
+                                            int bh, int x, int n_wg, const SparseRegs<PRE>& r,
+                                            SparseSmem<D, GC, PRE>& sm, float* __restrict__ part,
                                             int stride,
                                             const int32_t* __restrict__ table = nullptr) {
   constexpr int MT = D / 16;
@@ -776,9 +778,9 @@ __device__ __forceinline__ void sparse_body(const Dims& m, float s,
   // them, and it then waits for every store before the record's next ones
   if (kv.n_valid > 0) {
     sparse_load<D, BLK>(m, kc, vc, blk, bh, x, table, kv);
-    sparse_mma<D, GC>(s, kv, sm, acc_o, m_run, l_run);
+    sparse_mma<D, GC, PRE>(s, kv, sm, acc_o, m_run, l_run);
   }
-  sparse_record<D, CO, GC>(m, acc_o, m_run, l_run, bh, x, n_wg, r, sm, part, stride);
+  sparse_record<D, CO, GC, PRE>(m, acc_o, m_run, l_run, bh, x, n_wg, r, sm, part, stride);
 }
 
 }  // namespace spla
