@@ -785,6 +785,7 @@ __device__ __forceinline__ void group_walk(const GroupArgs& a, int bh, GroupWave
 #pragma unroll
           for (int ks = 0; ks < KS; ++ks) {
             const bf16x8 qh = operand(1, ks), ql = operand(2, ks);
+            bf16x8 fh[2], fl[2];
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
               float f[8];
@@ -794,14 +795,18 @@ __device__ __forceinline__ void group_walk(const GroupArgs& a, int bh, GroupWave
                 f[e] = __builtin_amdgcn_exp2f(decltype(shifted)::v ? fmaf(k, kLog2e, -mxl[mt])
                                                                    : k * kLog2e);
               }
-              bf16x8 fh, fl;
-              split_bf16x8(f, fh, fl);
-              sl[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl, qh, sl[mt], 0, 0, 0);
-              su[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl, ones, su[mt], 0, 0, 0);
-              sl[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, ql, sl[mt], 0, 0, 0);
-              su[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, ones, su[mt], 0, 0, 0);
-              sl[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, qh, sl[mt], 0, 0, 0);
+              split_bf16x8(f, fh[mt], fl[mt]);
             }
+            auto both = [&](floatx4 (&acc)[2], const bf16x8 (&x)[2], const bf16x8& y) {
+#pragma unroll
+              for (int mt = 0; mt < 2; ++mt)
+                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[mt], y, acc[mt], 0, 0, 0);
+            };
+            both(sl, fl, qh);
+            both(su, fl, ones);
+            both(sl, fh, ql);
+            both(su, fh, ones);
+            both(sl, fh, qh);
           }
         };
         weights(Idx<0>{});
@@ -811,7 +816,14 @@ __device__ __forceinline__ void group_walk(const GroupArgs& a, int bh, GroupWave
           lo = fminf(lo, su[e >> 2][e & 3]);
           hi = fmaxf(hi, su[e >> 2][e & 3]);
         }
-        if (__ballot(!(lo > 0x1p-64f && hi < 0x1p64f)) != 0ull) weights(Idx<1>{});
+        if (__ballot(!(lo > 0x1p-64f && hi < 0x1p64f)) != 0ull) {
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            forget(ka[0][ks]);
+            forget(ka[1][ks]);
+          }
+          weights(Idx<1>{});
+        }
         float wv[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
