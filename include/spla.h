@@ -246,9 +246,9 @@ int32_t spla_decode_phase_mask(const spla_config* cfg, uint32_t* out_mask);
 int32_t spla_append_workspace_bytes(const spla_config* cfg, int32_t max_new, size_t* out_bytes);
 
 /* Device workspace that spla_prefill needs for n_tokens positions per
- * sequence (host-only query): per-query scores, selections, records and
- * global terms of one chunk of at most 32 positions for the chunked shapes,
- * the decode workspace for the others. */
+ * sequence (host-only query): per-query scores, selections and records and the
+ * global terms of one chunk for the chunked shapes, the decode workspace for
+ * the others. It grows with n_tokens. */
 int32_t spla_prefill_workspace_bytes(const spla_config* cfg, int32_t n_tokens,
                                      size_t* out_bytes);
 
@@ -345,8 +345,8 @@ int32_t spla_step(const spla_config* cfg, const spla_cache* cache, const void* k
  * per-query top-k, and the fused sparse kernel over groups of consecutive
  * queries, which share the blocks that more than one of them selects); other
  * shapes (which never decode in one launch) run the positions one at a time as
- * spla_step does, on the separate decode launches. n_tokens = 0 does nothing; tokens past max_seq_len
- * are dropped as in spla_step (SPLA_DEVERR_CAPACITY) and the queries at those
+ * spla_step does, on the separate decode launches. n_tokens = 0 does nothing;
+ * tokens past max_seq_len are dropped as in spla_step (SPLA_DEVERR_CAPACITY) and the queries at those
  * positions decode over the full cache. */
 int32_t spla_prefill(const spla_config* cfg, const spla_cache* cache, int32_t n_tokens,
                      const void* k_new, const void* v_new, const void* q,
