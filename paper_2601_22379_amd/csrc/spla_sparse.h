@@ -25,8 +25,6 @@
 // wavefronts take consecutive steps.
 #pragma once
 
-#include <type_traits>
-
 #include "spla_device.h"
 
 namespace spla {
@@ -584,124 +582,77 @@ __device__ __forceinline__ void sparse_load(const Dims& m, const bf16_t* __restr
 // The two products of one step (n_valid > 0): S = K [q | phi(q)]^T, the
 // step's softmax over the exact columns, and acc_o = V^T P; m_run / l_run get
 // the step's max and sum (exact columns) or the sum of the linear weights.
-// ONLINE: acc_o, m_run and l_run already hold earlier steps of this
-// wavefront; the exact columns are rescaled to the running max first.
-// keys_used() runs when the step's keys are no longer needed (to load others).
-// exp(k) goes k-step by k-step straight into its products, the row sums of
-// phi(k) from the same operands times ones. The exponentials are taken
-// unshifted (normalising cancels any shift); a step with a row sum far from 1
-// takes them again, shifted by the row's maximum. (With the shift, the sums and
-// the reciprocals on the vector unit a step took about 800 vector instructions
-// instead of 600: 32K decode 23.3 -> 22.5 us, 128K 29.5 -> 29.05 us.)
-struct NoHook {
-  __device__ void operator()() const {}
-};
-
-template <int D, int GC, int PRE, bool ONLINE = false, typename HOOK = NoHook>
+// phi(k) is taken row by row, relative to the row's maximum and with its sum in
+// fp32: a row that lies past the length, whatever it holds, then touches no other
+// row's bits. (Unshifted exponentials with the sums on the matrix cores, shifted
+// for a whole step where a sum is far from 1, took 22.5 us against 23.2 at 32K,
+// 29.0 against 29.5 at 128K, but a stale row decided the other rows' rounding.)
+template <int D, int GC, int PRE>
 __device__ __forceinline__ void sparse_mma(float s, SparseKV<D>& kv, SparseSmem<D, GC, PRE>& sm,
                                            floatx4 (&acc_o)[D / 16], float& m_run,
-                                           float& l_run, const HOOK& keys_used = HOOK{}) {
+                                           float& l_run) {
   constexpr int KS = D / 32;     // k-steps of the first product
   constexpr int MT = D / 16;     // coordinate tiles of the second product
   const int lane = threadIdx.x & 63;
   const int j = lane & 15, g = lane >> 4;
   const bool exact_col = j < 8;
   const int n_valid = kv.n_valid;
-  bf16x8 ones;
+  floatx4 sw[2];
+  float zinv[2];  // 1 / sum exp(k - max k) of this lane's key row, per tile
 #pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
-  // logits and weights; sums of exp(k) of the rows. The two tiles' products
-  // alternate, so that none waits for the one just issued
-  floatx4 sw[2], su[2];
-  auto products = [&](auto shifted) {
-    float mxl[2] = {0.f, 0.f};
+  for (int mt = 0; mt < 2; ++mt) {
+    sw[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      sw[mt] = su[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-      if constexpr (decltype(shifted)::value) {
-        float mx = -INFINITY;
+    for (int ks = 0; ks < KS; ++ks)
+      sw[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          kv.ka[mt][ks], __builtin_bit_cast(bf16x8, sm.qops[0][ks][lane]), sw[mt], 0, 0, 0);
+    // exp(k - max k) of this lane's key row (row i of the tile), spread over
+    // lanes i + 16 g'; the 1 / sum of phi(k) is applied to the result rows
+    float mx = -INFINITY;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+    for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) mx = fmaxf(mx, (float)kv.ka[mt][ks][e]);
-        mx = fmaxf(mx, xor16(mx));
-        mx = fmaxf(mx, xor32(mx));
-        mxl[mt] = mx * kLog2e;
+      for (int e = 0; e < 8; ++e) mx = fmaxf(mx, (float)kv.ka[mt][ks][e]);
+    mx = fmaxf(mx, xor16(mx));
+    mx = fmaxf(mx, xor32(mx));
+    const float mxl = mx * kLog2e;
+    // exp(k - max k) k-step by k-step, each step straight into its products
+    float sum = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      bf16x8 fh, fl;
+      float f[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        f[e] = __builtin_amdgcn_exp2f(fmaf((float)kv.ka[mt][ks][e], kLog2e, -mxl));
+        sum += f[e];
       }
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const bf16x8 qv = __builtin_bit_cast(bf16x8, sm.qops[0][ks][lane]);
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-        sw[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv.ka[mt][ks], qv, sw[mt], 0, 0, 0);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
+      split_bf16x8(f, fh, fl);
       const bf16x8 ph = __builtin_bit_cast(bf16x8, sm.qops[1][ks][lane]);
       const bf16x8 pl = __builtin_bit_cast(bf16x8, sm.qops[2][ks][lane]);
-      bf16x8 fh[2], fl[2];
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        float f[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float k = (float)kv.ka[mt][ks][e];
-          f[e] = __builtin_amdgcn_exp2f(decltype(shifted)::value ? fmaf(k, kLog2e, -mxl[mt])
-                                                                 : k * kLog2e);
-        }
-        split_bf16x8(f, fh[mt], fl[mt]);
-      }
-      auto both = [&](floatx4 (&acc)[2], const bf16x8 (&x)[2], const bf16x8& y) {
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-          acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[mt], y, acc[mt], 0, 0, 0);
-      };
-      both(sw, fl, ph);
-      both(su, fl, ones);
-      both(sw, fh, pl);
-      both(su, fh, ones);
-      both(sw, fh, ph);
+      sw[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, ph, sw[mt], 0, 0, 0);
+      sw[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, pl, sw[mt], 0, 0, 0);
+      sw[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl, ph, sw[mt], 0, 0, 0);
     }
-  };
-  products(std::false_type{});
-  float lo = su[0][0], hi = su[0][0];
-#pragma unroll
-  for (int e = 1; e < 8; ++e) {
-    lo = fminf(lo, su[e >> 2][e & 3]);
-    hi = fmaxf(hi, su[e >> 2][e & 3]);
+    sum += xor16(sum);
+    sum += xor32(sum);
+    zinv[mt] = 1.0f / sum;
   }
-  if (__ballot(!(lo > 0x1p-64f && hi < 0x1p64f)) != 0ull) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      forget(kv.ka[0][ks]);
-      forget(kv.ka[1][ks]);
-    }
-    products(std::true_type{});
-  }
-  keys_used();
   // tokens 8g .. 8g+7 of this step: tile 0 rows 4g..4g+3, tile 1 rows 4g..4g+3
-  // (result row 4g + r of tile t is token 8g + 4t + r)
+  // (result row 4g + r of tile t is token 8g + 4t + r; its 1 / Z sits in
+  // lane 4g + r)
   float val[8];
   float cmax = -INFINITY;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const bool ok = 8 * g + e < n_valid;
+    const float zi = __shfl(zinv[e >> 2], 4 * g + (e & 3), kWave);
     const float xx = sw[e >> 2][e & 3];
-    const float zi = __builtin_amdgcn_rcpf(su[e >> 2][e & 3]);
     val[e] = exact_col ? (ok ? xx * s : -INFINITY) : (ok ? xx * zi : 0.f);
     cmax = fmaxf(cmax, val[e]);
   }
   cmax = fmaxf(cmax, xor16(cmax));
   cmax = fmaxf(cmax, xor32(cmax));
-  float alpha = 1.f;  // ONLINE: the earlier steps' scale (exact columns)
-  if constexpr (ONLINE) {
-    if (exact_col) {
-      const float mn = fmaxf(m_run, cmax);
-      alpha = m_run == -INFINITY ? 0.f : __expf(m_run - mn);
-      cmax = mn;
-    }
-  }
   float psum = 0.f;
   bf16x8 bh8, bl8;
   float pv[8];
@@ -713,13 +664,7 @@ __device__ __forceinline__ void sparse_mma(float s, SparseKV<D>& kv, SparseSmem<
   split_bf16x8(pv, bh8, bl8);
   psum += xor16(psum);
   psum += xor32(psum);
-  if constexpr (ONLINE) {
-#pragma unroll
-    for (int t = 0; t < MT; ++t) acc_o[t] = acc_o[t] * alpha;
-    l_run = fmaf(l_run, alpha, psum);
-  } else {
-    l_run = psum;
-  }
+  l_run = psum;
   m_run = exact_col ? cmax : -INFINITY;
   if (n_valid < 32) {  // rows past the sequence end may hold anything: zero them
 #pragma unroll
