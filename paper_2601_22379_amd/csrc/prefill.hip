@@ -676,9 +676,6 @@ __device__ __forceinline__ void group_walk(const GroupArgs& a, int bh, GroupWave
   constexpr int KS = D / 32, MT = D / 16, CPB = BLK / 32;
   const Dims& m = a.m;
   const int lane = threadIdx.x & 63, lg = lane >> 4;
-  bf16x8 ones;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
   for (int seg = 0; seg < s.nbg; seg += kSegBlocks) {
     // ---- the union of the positions' selections within this segment
     const int ns = min(kSegBlocks, s.nbg - seg);
@@ -768,75 +765,49 @@ __device__ __forceinline__ void group_walk(const GroupArgs& a, int bh, GroupWave
         sx[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[1][ks], qx, sx[1], 0, 0, 0);
       }
       if constexpr (LIN) {
-        // linear weights: exp(k) k-step by k-step, straight into its products,
-        // the row sums from the same operands times ones. The exponentials are
-        // taken unshifted (normalising cancels any shift); a step with a row
-        // sum far from 1 takes them again, shifted by the row's maximum.
-        floatx4 sl[2], su[2];
-        auto weights = [&](auto shifted) {
-          float mxl[2] = {0.f, 0.f};
+        // linear weights: exp(k - max k) k-step by k-step, straight into its
+        // products; each lane sums its part of its key row (row lane % 16 of
+        // the tile), and 1 / sum is applied to the result rows
+        floatx4 sl[2];
+        float zinv[2];
 #pragma unroll
-          for (int mt = 0; mt < 2; ++mt) {
-            sl[mt] = su[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (decltype(shifted)::v) {
-              float mx = -INFINITY;
+        for (int mt = 0; mt < 2; ++mt) {
+          sl[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+          float mx = -INFINITY;
 #pragma unroll
-              for (int ks = 0; ks < KS; ++ks)
+          for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) mx = fmaxf(mx, (float)ka[mt][ks][e]);
-              mx = fmaxf(mx, xor16(mx));
-              mx = fmaxf(mx, xor32(mx));
-              mxl[mt] = mx * kLog2e;
-            }
-          }
+            for (int e = 0; e < 8; ++e) mx = fmaxf(mx, (float)ka[mt][ks][e]);
+          mx = fmaxf(mx, xor16(mx));
+          mx = fmaxf(mx, xor32(mx));
+          const float mxl = mx * kLog2e;
+          float sum = 0.f;
 #pragma unroll
           for (int ks = 0; ks < KS; ++ks) {
+            float f[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              f[e] = __builtin_amdgcn_exp2f(fmaf((float)ka[mt][ks][e], kLog2e, -mxl));
+              sum += f[e];
+            }
+            bf16x8 fh, fl;
+            split_bf16x8(f, fh, fl);
             const bf16x8 qh = operand(1, ks), ql = operand(2, ks);
-            bf16x8 fh[2], fl[2];
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-              float f[8];
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                const float k = (float)ka[mt][ks][e];
-                f[e] = __builtin_amdgcn_exp2f(decltype(shifted)::v ? fmaf(k, kLog2e, -mxl[mt])
-                                                                   : k * kLog2e);
-              }
-              split_bf16x8(f, fh[mt], fl[mt]);
-            }
-            auto both = [&](floatx4 (&acc)[2], const bf16x8 (&x)[2], const bf16x8& y) {
-#pragma unroll
-              for (int mt = 0; mt < 2; ++mt)
-                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[mt], y, acc[mt], 0, 0, 0);
-            };
-            both(sl, fl, qh);
-            both(su, fl, ones);
-            both(sl, fh, ql);
-            both(su, fh, ones);
-            both(sl, fh, qh);
+            sl[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl, qh, sl[mt], 0, 0, 0);
+            sl[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, ql, sl[mt], 0, 0, 0);
+            sl[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, qh, sl[mt], 0, 0, 0);
           }
-        };
-        weights(Idx<0>{});
-        float lo = su[0][0], hi = su[0][0];
-#pragma unroll
-        for (int e = 1; e < 8; ++e) {
-          lo = fminf(lo, su[e >> 2][e & 3]);
-          hi = fmaxf(hi, su[e >> 2][e & 3]);
-        }
-        if (__ballot(!(lo > 0x1p-64f && hi < 0x1p64f)) != 0ull) {
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks) {
-            forget(ka[0][ks]);
-            forget(ka[1][ks]);
-          }
-          weights(Idx<1>{});
+          sum += xor16(sum);
+          sum += xor32(sum);
+          zinv[mt] = 1.0f / sum;
         }
         float wv[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int tt = 8 * lg + e;         // token of the step
           const bool in = base + tt < s.tb;  // in S_x
-          const float wt = sl[e >> 2][e & 3] * __builtin_amdgcn_rcpf(su[e >> 2][e & 3]);
+          const float zi = __shfl(zinv[e >> 2], 4 * lg + (e & 3), kWave);
+          const float wt = sl[e >> 2][e & 3] * zi;
           float v = in ? (sel ? wt : 0.f) : (cur && !sel ? -wt : 0.f);
           v = tt < nvis ? v : 0.f;
           wv[e] = v;

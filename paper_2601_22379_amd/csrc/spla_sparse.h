@@ -54,14 +54,6 @@ __device__ __forceinline__ void split_bf16x8(const float (&x)[8], bf16x8& hi, bf
   lo = __builtin_bit_cast(bf16x8, make_uint4(lp[0], lp[1], lp[2], lp[3]));
 }
 
-// The same values, as far as the compiler knows new ones: what is computed from
-// them is computed again instead of being kept in registers from an earlier use.
-__device__ __forceinline__ void forget(bf16x8& x) {
-  uint4 u = __builtin_bit_cast(uint4, x);
-  asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(u.z), "+v"(u.w));
-  x = __builtin_bit_cast(bf16x8, u);
-}
-
 // Rows of S_bar owned by workgroup x of n_wg: row0 .. row0 + nrows - 1.
 __device__ __forceinline__ void lin_rows(int D, int x, int n_wg, int* row0, int* nrows) {
   const int rw = (D + n_wg - 1) / n_wg;

@@ -51,3 +51,17 @@ def test_decode_and_step(name):
         return (*cache.decode(q, gamma), *cache.step(*rows, q, gamma), cache.state, cache.stats)
 
     both(name, call)
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_prefill(name):
+    def call(w, cache, dev):
+        T = 3  # the last step holds rows of the prefix: those carry linear weights
+        q = torch.cat([H.to_dev(si.gen_q_batch(w, t), w, dev)[None] for t in range(T)])
+        g = torch.Generator().manual_seed(4)
+        rows = [torch.randn((T, w.batch, w.n_kv_heads, w.head_dim), generator=g).to(dev, q.dtype)
+                for _ in range(2)]
+        return (*cache.prefill(*rows, q, torch.from_numpy(si.gen_gamma(w)).to(dev)), cache.state,
+                cache.norm, cache.stats)
+
+    both(name, call)
