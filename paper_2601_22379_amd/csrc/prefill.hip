@@ -162,7 +162,10 @@ __global__ __launch_bounds__(256) void prefill_prefix_kernel(
     float* __restrict__ z_pre, int32_t* __restrict__ near) {
   constexpr int KS = D / 32, PER = D * D / 8;  // operand pieces per block
   const int bh = blockIdx.y;
-  if (bh == 0 && blockIdx.x == 0 && threadIdx.x == 0) near[0] = 0;  // for the selection
+  if (blockIdx.x == 0 && threadIdx.x == 0) {  // for the selection
+    near[bh] = 0;
+    if (bh == 0) near[m.bh] = 0;
+  }
   int L0, nv;
   chunk_bounds(m, seq_lens, bh / m.hkv, T_, &L0, &nv);
   if (nv <= 0 && !lin) return;
@@ -447,7 +450,8 @@ struct PrefSelectArgs {
   const float* e_vals;
   const double* tile_part;
   int32_t *sel_ws, *sel_out;
-  int32_t* near;  // [0]: listed queries, [1 ..]: their rows bh T + i
+  int32_t* near;  // [bh]: listed queries of each (sequence, KV head); the longest list;
+                  // [bh][T]: their positions
   int listed;     // select the listed queries (else every query, listing some)
 };
 
@@ -461,14 +465,18 @@ __global__ __launch_bounds__(NT) void prefill_select_kernel(PrefSelectArgs a) {
     chunk_bounds(m, a.seq_lens, vh / a.T / m.hkv, a.T, &L0, &nv);
     return L0 + min(vh % a.T + 1, nv);
   };
-  // this workgroup's queries; those whose blocks all fit in k first, as one
-  // run of stores
-  const int n_q = a.listed ? a.near[0] : m.bh * a.T, per = (n_q - 1) / (int)gridDim.x + 1;
-  const int q0 = (int)blockIdx.x * per, q1 = min(q0 + per, n_q);
-  if (q0 >= q1) return;
+  // this workgroup's queries: a run of them, those whose blocks all fit in k
+  // first, as one run of stores; or every gridDim.x-th entry of the lists, entry
+  // x / bh of the list of x % bh (short lists spread over the workgroups)
+  int32_t* list = a.near + m.bh + 1;
+  const int n_q = m.bh * a.T, per = (n_q - 1) / (int)gridDim.x + 1;
+  const int x0 = a.listed ? (int)blockIdx.x : (int)blockIdx.x * per;
+  const int x1 = a.listed ? m.bh * a.near[m.bh] : min(x0 + per, n_q);
+  const int step = a.listed ? (int)gridDim.x : 1;
+  if (x0 >= x1) return;
   if (!a.listed && per > 1) {
-    for (int x = threadIdx.x; x < (q1 - q0) * m.k; x += NT) {
-      const int vh = q0 + x / m.k, e = x % m.k, nb = (length(vh) + m.B - 1) / m.B;
+    for (int x = threadIdx.x; x < (x1 - x0) * m.k; x += NT) {
+      const int vh = x0 + x / m.k, e = x % m.k, nb = (length(vh) + m.B - 1) / m.B;
       if (nb <= m.k) {
         a.sel_ws[(int64_t)vh * m.k + e] = e < nb ? e : -1;
         if (a.sel_out)
@@ -476,17 +484,25 @@ __global__ __launch_bounds__(NT) void prefill_select_kernel(PrefSelectArgs a) {
       }
     }
     // (lengths grow along a run of one (sequence, KV head))
-    if (q0 / a.T == (q1 - 1) / a.T && (length(q1 - 1) + m.B - 1) / m.B <= m.k) return;
+    if (x0 / a.T == (x1 - 1) / a.T && (length(x1 - 1) + m.B - 1) / m.B <= m.k) return;
   }
-  for (int x = q0; x < q1; ++x) {
-    const int vh = a.listed ? a.near[1 + x] : x, bh = vh / a.T, i = vh % a.T;
-    const int L = length(vh);
-    if (per > 1 && (L + m.B - 1) / m.B <= m.k) continue;  // uniform; written above
+  for (int x = x0; x < x1; x += step) {
+    int vh = x;
+    if (a.listed) {
+      if (x / m.bh >= a.near[x % m.bh]) continue;  // uniform
+      vh = x % m.bh * a.T + list[(int64_t)(x % m.bh) * a.T + x / m.bh];
+    }
+    const int bh = vh / a.T, i = vh % a.T, L = length(vh);
+    if (!a.listed && per > 1 && (L + m.B - 1) / m.B <= m.k) continue;  // uniform; written above
     const bool near = select_blocks<NT, R, SWN, false, 0, WIN, GMAX>(
         m, vh, L, a.e_vals, a.tile_part, sm, a.sel_ws + (int64_t)vh * m.k, nullptr,
         a.sel_out ? a.sel_out + ((int64_t)i * m.bh + bh) * m.k : nullptr, wsc,
         a.listed ? 0.f : kTieSpan);
-    if (near && threadIdx.x == 0) a.near[1 + atomicAdd(a.near, 1)] = vh;
+    if (near && threadIdx.x == 0) {
+      const int j = atomicAdd(a.near + bh, 1);
+      list[(int64_t)bh * a.T + j] = i;
+      atomicMax(a.near + m.bh, j + 1);
+    }
     __syncthreads();  // the next query's selection writes the same LDS
   }
 }
@@ -495,68 +511,99 @@ __global__ __launch_bounds__(NT) void prefill_select_kernel(PrefSelectArgs a) {
 // sums: v_mfma_f32_16x16x4_f32 adds its four products to the accumulator one
 // fused multiply-add at a time in coordinate order, so two of them are the
 // decode's eight-coordinate fp32 partial sum bit for bit, and those partials
-// are added in fp64. One workgroup per (statistics tile, listed query),
-// wavefront w taking units 16 w .. 16 w + 15 as rows (operands straight from
-// the statistics: lane holds unit lane % 16, coordinate 4 j + lane / 16 of
-// k-step j); the columns are the query's heads.
+// are added in fp64. One workgroup per (statistics tile, share of the list,
+// sequence x KV head), wavefront w taking units 16 w .. 16 w + 15 as rows
+// (operands straight from the statistics: lane holds unit lane % 16, coordinate
+// 4 j + lane / 16 of k-step j), kept in registers; the columns are the heads of
+// as many listed queries as 16 hold (kP), their coefficients staged in LDS.
+// Where blocks repeat, every query can be listed (ties at the cutoff): 8192
+// queries over 32 tiles of 64 blocks took 7400 us with one query's G columns at
+// a time, 820 with kP.
 template <int D>
-__global__ __launch_bounds__(256) void prefill_rescore_kernel(
+__global__ __launch_bounds__(256, 2) void prefill_rescore_kernel(
     Dims m, int T_, int W, const float* __restrict__ stats, const int32_t* __restrict__ seq_lens,
     const bf16_t* __restrict__ q, double s, int first_order, const double* __restrict__ ell_part,
     const int32_t* __restrict__ near, float* __restrict__ e_vals, double* __restrict__ tile_part) {
   constexpr int NK = D / 4, NQ = D / 32;  // k-steps, partials per quarter of the coordinates
+  __shared__ float s_c[2][NK][64];        // s q and s^2 q^2 / 2, as operands
   __shared__ double s_mx[4][16], s_sum[4][16];
-  const int G = m.group, nbp = m.n_tiles * kTileBlocks;
+  const int G = m.group, kP = 16 / G, nbp = m.n_tiles * kTileBlocks;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int li = lane & 15, lg = lane >> 4, g = min(li, G - 1);
-  const int tile = blockIdx.x, n_near = near[0];
-  for (int x = blockIdx.y; x < n_near; x += gridDim.y) {
-    const int vh = near[1 + x], bh = vh / T_, i = vh % T_;
-    int L0, nv;
-    chunk_bounds(m, seq_lens, bh / m.hkv, T_, &L0, &nv);
-    const int L = L0 + min(i + 1, nv), nu = (L + m.us - 1) / m.us;
-    if (tile * kTileBlocks >= nu) continue;  // uniform
-    const int64_t o = stats_off4(m, bh, (int64_t)tile * kTileBlocks + 16 * w + li, 0, 0) + lg;
-    const float* pm = stats + o;
-    const float* pv = stats + (first_order ? o : o + (int64_t)(D / 4) * kTileBlocks * 4);
-    const bf16_t* qr =
-        q + (((int64_t)i * m.batch + bh / m.hkv) * m.hq + bh % m.hkv * G + g) * D + lg;
-    double am[4][4], av[4][4];  // quarter of the coordinates, result row
+  const int li = lane & 15, lg = lane >> 4;
+  const int tile = blockIdx.x, bh = blockIdx.z, n_near = near[bh];
+  if ((int)blockIdx.y * kP >= n_near) return;
+  int L0, nv;
+  chunk_bounds(m, seq_lens, bh / m.hkv, T_, &L0, &nv);
+  if (tile * kTileBlocks * m.us >= L0 + nv) return;  // past every query's tokens
+  const int32_t* list = near + m.bh + 1 + (int64_t)bh * T_;
+  float pm[NK], pv[NK];
+  {
+    const float* st = stats + stats_off4(m, bh, (int64_t)tile * kTileBlocks, 0, 0);  // uniform
+    const float* st2 = first_order ? st : st + D / 4 * kTileBlocks * 4;
+    const uint32_t o = (uint32_t)(16 * w + li) * 4u + (uint32_t)lg;
 #pragma unroll
-    for (int qt = 0; qt < 4; ++qt) {
+    for (int j = 0; j < NK; ++j) {
+      pm[j] = (st + j * kTileBlocks * 4)[o];
+      pv[j] = (st2 + j * kTileBlocks * 4)[o];
+    }
+  }
+  const int u_lane = tile * kTileBlocks + 16 * w + 4 * lg;  // this lane's first result row
+  for (int x0 = (int)blockIdx.y * kP; x0 < n_near; x0 += (int)gridDim.y * kP) {
+    const int nc = min(kP, n_near - x0) * G;  // columns in use
+    {
+      const int c = min(li, nc - 1), g = c % G;
+      const bf16_t* qr = q + (((int64_t)list[x0 + c / G] * m.batch + bh / m.hkv) * m.hq +
+                              bh % m.hkv * G + g) * D + lg;
 #pragma unroll
-      for (int rr = 0; rr < 4; ++rr) am[qt][rr] = av[qt][rr] = 0.0;
+      for (int jj = 0; jj < NK / 4; ++jj) {
+        const int j = 4 * jj + w;
+        const double xq = (double)bf16_to_f32(qr[4 * j].bits);
+        s_c[0][j][lane] = (float)(s * xq);
+        s_c[1][j][lane] = (float)(0.5 * s * s * xq * xq);
+      }
+    }
+    __syncthreads();
+    double am[2][4], av[2][4];  // quarters qt and qt + 2 of the coordinates added, result row
+#pragma unroll
+    for (int qp = 0; qp < 4; ++qp) {
+      const int qt = qp / 2 + 2 * (qp % 2);
+      double dm[4] = {0.0, 0.0, 0.0, 0.0}, dv[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int jp = 0; jp < NQ; ++jp) {
         floatx4 pa = {0.f, 0.f, 0.f, 0.f}, pb = pa;
 #pragma unroll
         for (int y = 0; y < 2; ++y) {
           const int j = 2 * (NQ * qt + jp) + y;
-          const double xq = (double)bf16_to_f32(qr[4 * j].bits);
-          pa = __builtin_amdgcn_mfma_f32_16x16x4f32(pm[j * kTileBlocks * 4], (float)(s * xq), pa,
-                                                    0, 0, 0);
-          pb = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[j * kTileBlocks * 4],
-                                                    (float)(0.5 * s * s * xq * xq), pb, 0, 0, 0);
+          pa = __builtin_amdgcn_mfma_f32_16x16x4f32(pm[j], s_c[0][j][lane], pa, 0, 0, 0);
+          pb = __builtin_amdgcn_mfma_f32_16x16x4f32(pv[j], s_c[1][j][lane], pb, 0, 0, 0);
         }
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
-          am[qt][rr] += (double)pa[rr];
-          av[qt][rr] += (double)pb[rr];
+          dm[rr] += (double)pa[rr];
+          dv[rr] += (double)pb[rr];
         }
       }
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        am[qp / 2][rr] = qp % 2 ? am[qp / 2][rr] + dm[rr] : dm[rr];
+        av[qp / 2][rr] = qp % 2 ? av[qp / 2][rr] + dv[rr] : dv[rr];
+      }
+      __builtin_amdgcn_sched_barrier(0);  // (operands of one quarter at a time in registers)
     }
-    const int u_lane = tile * kTileBlocks + 16 * w + 4 * lg;  // this lane's first result row
+    // this lane's column: position i, head g of the group
+    const int c = min(li, nc - 1), i = list[x0 + c / G], g = c % G;
+    const int64_t vh = (int64_t)bh * T_ + i;
+    const int L = L0 + min(i + 1, nv), nu = (L + m.us - 1) / m.us;
     double ell[4];
     float mx = -INFINITY;
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
       const int u = u_lane + rr, n = min(m.ul, max(L - u * m.us, 1));
-      // the quarters in the order the decode adds them
-      const double dm = (am[0][rr] + am[2][rr]) + (am[1][rr] + am[3][rr]);
-      const double dv = (av[0][rr] + av[2][rr]) + (av[1][rr] + av[3][rr]);
+      // the quarters in the order the decode adds them: (0 + 2) + (1 + 3)
+      const double dm = am[0][rr] + am[1][rr], dv = av[0][rr] + av[1][rr];
       double e = log_mass(dm, n, (float)dv * __builtin_amdgcn_rcpf((float)n), first_order);
       const int wu = (L0 + i) / m.us - u;
-      if (i < nv && wu >= 0 && wu < W) e = ell_part[((int64_t)vh * W + wu) * G + g];
+      if (i < nv && wu >= 0 && wu < W) e = ell_part[(vh * W + wu) * G + g];
       ell[rr] = u < nu ? e : -INFINITY;
       mx = fmaxf(mx, (float)ell[rr]);
     }
@@ -574,20 +621,19 @@ __global__ __launch_bounds__(256) void prefill_rescore_kernel(
       e[rr] = exp_mass(ell[rr], tmx);
       sum += (double)e[rr];
     }
-    if (li < G)
-      *reinterpret_cast<float4*>(e_vals + ((int64_t)vh * G + li) * nbp + u_lane) =
+    // (a tile past this position's tokens gets zeros, which nothing reads)
+    if (li < nc)
+      *reinterpret_cast<float4*>(e_vals + (vh * G + g) * nbp + u_lane) =
           make_float4(e[0], e[1], e[2], e[3]);
     sum += xor16(sum);
     sum += xor32(sum);
     if (lg == 0) s_sum[w][li] = sum;
     __syncthreads();
-    if (tid < G) {
+    if (tid < nc) {
       for (int y = 1; y < 4; ++y) sum = (y == 1 ? s_sum[0][tid] : sum) + s_sum[y][tid];
-      double2* tp = reinterpret_cast<double2*>(tile_part) +
-                    ((int64_t)vh * G + tid) * m.n_tiles + tile;
+      double2* tp = reinterpret_cast<double2*>(tile_part) + (vh * G + g) * m.n_tiles + tile;
       *tp = make_double2(tmx, sum);
     }
-    __syncthreads();
   }
 }
 
@@ -1112,7 +1158,8 @@ static void prefill_select_r(const PrefSelectArgs& a, hipStream_t st) {
   auto kern = a.m.group <= 4 ? prefill_select_kernel<R, WIN, NT, SWN, 4>
                              : prefill_select_kernel<R, WIN, NT, SWN, 8>;
   const int64_t queries = (int64_t)a.m.bh * a.T;
-  const int64_t most = (int64_t)compute_units() * (NT != 256 ? 8 : (a.listed ? 1 : 32));
+  // (the listed queries are few as a rule: fewer workgroups to start)
+  const int64_t most = (int64_t)compute_units() * (NT != 256 ? (a.listed ? 1 : 8) : (a.listed ? 4 : 32));
   hipLaunchKernelGGL(kern, dim3((unsigned)(queries < most ? queries : most)), dim3(NT), 0, st, a);
 }
 
@@ -1188,8 +1235,9 @@ static hipError_t prefill_chunk_d(const Dims& m, const spla_config& cfg, const s
   auto select = [&](auto f) {
     f(sa, st);
     sa.listed = 1;
-    hipLaunchKernelGGL((prefill_rescore_kernel<D>), dim3((unsigned)m.n_tiles, 16), dim3(256), 0,
-                       st, m, T, W, (const float*)c.blk_stats, (const int32_t*)c.seq_lens, q,
+    hipLaunchKernelGGL((prefill_rescore_kernel<D>),
+                       dim3((unsigned)m.n_tiles, (unsigned)(qs < n_cg ? qs : n_cg), (unsigned)m.bh),
+                       dim3(256), 0, st, m, T, W, (const float*)c.blk_stats, (const int32_t*)c.seq_lens, q,
                        s_score, fo, (const double*)(base + ws.ell_part), sa.near,
                        (float*)(base + ws.e_vals), (double*)(base + ws.tile_part));
     f(sa, st);

@@ -271,7 +271,8 @@ struct PrefillWs {
   int64_t e_vals;     // f32 [bh][T G][n_tiles*64]  per query row, as the decode's
   int64_t tile_part;  // f64 [bh][T G][n_tiles][2]
   int64_t sel;        // i32 [bh T][k]
-  int64_t near;       // i32 [1 + bh T]  queries whose selection is taken again: count, rows
+  int64_t near;       // i32 [bh], 1, [bh][T]  queries whose selection is taken again: count per
+                      //   (sequence, KV head), the largest count, their positions
   int64_t part_s;     // f32 [bh][n_blk][d][d]  phi(K)^T V of each block the chunk touches
   int64_t part_z;     // f32 [bh][n_blk][d]
   int64_t s_hi, s_lo; // bf16 [bh][n_blk][d d]  S_bar before each block, operand order
@@ -301,7 +302,7 @@ SPLA_HD PrefillWs prefill_ws_layout(const Dims& m, int n_tokens) {
   w.e_vals = take(row * w.T);
   w.tile_part = take(nq * m.n_tiles * m.group * 2 * 8);
   w.sel = take(nq * m.k * 4);
-  w.near = take((1 + nq) * 4);
+  w.near = take((m.bh + 1 + nq) * 4);
   w.part_s = take(nb * m.d * m.d * 4);
   w.part_z = take(nb * m.d * 4);
   w.s_hi = take(nb * m.d * m.d * 2);
