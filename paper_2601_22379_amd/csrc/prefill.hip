@@ -494,7 +494,7 @@ __global__ __launch_bounds__(NT) void prefill_select_kernel(PrefSelectArgs a) {
     }
     const int bh = vh / a.T, i = vh % a.T, L = length(vh);
     if (!a.listed && per > 1 && (L + m.B - 1) / m.B <= m.k) continue;  // uniform; written above
-    const bool near = select_blocks<NT, R, SWN, false, 0, WIN, GMAX>(
+    const bool near = select_blocks<NT, R, SWN, false, 0, WIN, GMAX, false, true>(
         m, vh, L, a.e_vals, a.tile_part, sm, a.sel_ws + (int64_t)vh * m.k, nullptr,
         a.sel_out ? a.sel_out + ((int64_t)i * m.bh + bh) * m.k : nullptr, wsc,
         a.listed ? 0.f : kTieSpan);

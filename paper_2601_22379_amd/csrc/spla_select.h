@@ -104,9 +104,8 @@ struct RadixPick {
 // start so that the lanes spread over the LDS banks), then the BPL bins of the
 // lane that holds the key are spread one per lane.
 template <int BPL>
-__device__ __forceinline__ RadixPick radix_pick(const uint32_t* hist, uint32_t need) {
+__device__ __forceinline__ RadixPick radix_pick(const uint32_t* hist, uint32_t need, int lane) {
   constexpr int NV = BPL / 4;
-  const int lane = threadIdx.x & 63;
   uint32_t c = 0u;
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
@@ -152,6 +151,7 @@ struct SelectSmem {
 template <int NT, int R>
 __device__ __forceinline__ void radix_cut(const uint32_t (&key)[R], uint32_t kp, uint32_t* hist,
                                           uint32_t& gt, uint32_t& eqv, uint32_t& eq_need) {
+  const int lane = threadIdx.x & 63;
   gt = 0xFFFFFFFFu;
   eqv = 0u;
   eq_need = 0u;
@@ -167,7 +167,7 @@ __device__ __forceinline__ void radix_cut(const uint32_t (&key)[R], uint32_t kp,
       if (__ballot(in) != 0ull) atomicAdd(&H[(key[r] >> sh) & msk], in ? 1u : 0u);
     }
     __syncthreads();
-    const RadixPick p = rd == 0 ? radix_pick<32>(H, need) : radix_pick<16>(H, need);
+    const RadixPick p = rd == 0 ? radix_pick<32>(H, need, lane) : radix_pick<16>(H, need, lane);
     if (rd == 0 && p.total < need) {
       gt = 0u;
       return;
@@ -208,9 +208,12 @@ __device__ __forceinline__ void radix_cut(const uint32_t (&key)[R], uint32_t kp,
 // loads them with the first head's. GEX: the group is GMAX exactly.
 // near_span > 0: where the cutoff separates two scores closer than near_span
 // (relative), nothing is written and the result is true (in every thread);
-// otherwise it is false.
+// otherwise it is false. LOOP: for a workgroup that selects several queries in
+// turn; the thread's index is opaque, so that the addresses and masks it gives
+// are formed anew each time (kept over the loop they took up to 105 registers
+// more, and up to 125 spilled at 1024 threads).
 template <int NT, int R, int SWN, bool CO, int SEL_OFF = 0, bool WIN = false,
-          int GMAX = SPLA_MAX_GROUP, bool GEX = false>
+          int GMAX = SPLA_MAX_GROUP, bool GEX = false, bool LOOP = false>
 __device__ bool select_blocks(const Dims& m, int bh, int seq_len,
                               const float* __restrict__ e_vals,
                               const double* __restrict__ tile_part, SelectSmem<NT, SWN>& sm,
@@ -225,7 +228,9 @@ __device__ bool select_blocks(const Dims& m, int bh, int seq_len,
   float* sw = sm.sw;
   uint32_t* hist = sm.hist;
   const int G = GEX ? GMAX : m.group, k = m.k;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int tid_ = threadIdx.x;
+  if constexpr (LOOP) asm volatile("" : "+v"(tid_));
+  const int tid = tid_, lane = tid & 63, w = LOOP ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const int nbp = m.n_tiles * kTileBlocks;
   const int i0 = tid * R;
   const int kp = k - m.n_sink - m.n_local;
@@ -452,7 +457,7 @@ __device__ bool select_blocks(const Dims& m, int bh, int seq_len,
         if (__ballot(in) != 0ull) atomicAdd(&H[(key[r] >> sh) & msk], in ? 1u : 0u);
       }
       __syncthreads();
-      const RadixPick p = rd == 0 ? radix_pick<32>(H, need) : radix_pick<16>(H, need);
+      const RadixPick p = rd == 0 ? radix_pick<32>(H, need, lane) : radix_pick<16>(H, need, lane);
       if (rd == 0 && p.total < need) {  // fewer candidates than kp: take all
         gt = 0u;
         break;
