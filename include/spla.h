@@ -330,7 +330,11 @@ int32_t spla_step(const spla_config* cfg, const spla_cache* cache, const void* k
  * is appended at position L_b + t, and the queries at that position get
  * exactly what spla_step would give them there: they see the tokens up to and
  * including their own, with their own block selection, the statistics of
- * their partial blocks up to their position and S_bar over their prefix.
+ * their partial blocks up to their position and S_bar over their prefix. The
+ * selection of the chunked shapes is that of spla_decode after one spla_append
+ * of the rows up to the position; spla_step rounds the statistics of a block in
+ * progress to fp32 after every token, which can order differently scores whose
+ * logits agree to the last bits of their partial sums.
  *  k_new, v_new: device, dtype [n_tokens][batch][Hkv][d] (position-major).
  *  q:            device, dtype [n_tokens][batch][Hq][d].
  *  rms_weight:   device fp32 [Hq][d].

@@ -49,6 +49,15 @@ __device__ __forceinline__ int first_touched_unit(const Dims& m, int L0) {
 
 constexpr float kLn2f32 = 0.69314718055994531f;
 
+// The queries whose selection is taken again (PrefillWs::near): how many of each
+// (sequence, KV head), the largest count, their positions.
+struct NearLists {
+  int32_t *count, *longest, *list;
+};
+SPLA_HD NearLists near_lists(const Dims& m, int32_t* near) {
+  return {near, near + m.bh, near + m.bh + 1};
+}
+
 // ln n + ln(1 + x) as the decode's scoring takes them (hardware log2)
 __device__ __forceinline__ double log_mass(double mean_term, int n, float x, int first_order) {
   double ell = mean_term + (double)(__builtin_amdgcn_logf((float)n) * kLn2f32);
@@ -163,8 +172,9 @@ __global__ __launch_bounds__(256) void prefill_prefix_kernel(
   constexpr int KS = D / 32, PER = D * D / 8;  // operand pieces per block
   const int bh = blockIdx.y;
   if (blockIdx.x == 0 && threadIdx.x == 0) {  // for the selection
-    near[bh] = 0;
-    if (bh == 0) near[m.bh] = 0;
+    const NearLists nl = near_lists(m, near);
+    nl.count[bh] = 0;
+    if (bh == 0) *nl.longest = 0;
   }
   int L0, nv;
   chunk_bounds(m, seq_lens, bh / m.hkv, T_, &L0, &nv);
@@ -242,7 +252,7 @@ __device__ __forceinline__ void split3_bf16x8(const float (&x)[8], bf16x8& a, bf
 // coordinates the products of q . mu and q^2 . M2 accumulate in fp32 from the
 // small pieces to the large; the four partial sums of q . mu are added in
 // fp64. The log masses carry about as much rounding as the decode's but not
-// the same, which the selection makes up for where it matters (kTieSpan).
+// the same, which the selection makes up for where it matters (tie_span).
 // Units in progress at a query's position take their log mass from ell_part.
 // Results as the decode's scoring leaves them: exp(ell - tile max) per query
 // row and unit, (max, sum) per row and tile.
@@ -262,7 +272,8 @@ template <int D>
 __global__ __launch_bounds__(256, 2) void prefill_score_kernel(
     Dims m, int T_, int W, const float* __restrict__ stats, const int32_t* __restrict__ seq_lens,
     const bf16_t* __restrict__ q, double s, int first_order, const double* __restrict__ ell_part,
-    float* __restrict__ e_vals, double* __restrict__ tile_part) {
+    float* __restrict__ e_vals, double* __restrict__ tile_part, float2* __restrict__ unit_max,
+    float* __restrict__ q_norm2) {
   constexpr int KS = D / 32;
   __shared__ PrefScoreSmem<D> sm;
   const int tile = blockIdx.x, bh = blockIdx.z, b = bh / m.hkv, h = bh % m.hkv;
@@ -288,6 +299,28 @@ __global__ __launch_bounds__(256, 2) void prefill_score_kernel(
         y[ks][u] = *reinterpret_cast<const f32x4*>(
             stats + stats_off4(m, bh, blk, first_order ? 0 : 1, j4));
       }
+    if (blockIdx.y == 0) {  // for tie_span; a unit that is not finite counts as infinite
+      float n2 = 0.f, v = 0.f;
+      bool fine = true;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          n2 = fmaf(x[ks][e >> 2][e & 3], x[ks][e >> 2][e & 3], n2);
+          const float y1 = first_order ? 0.f : y[ks][e >> 2][e & 3];
+          v = fmaxf(v, y1);
+          fine = fine & (y1 < INFINITY);
+        }
+      n2 += xor16(n2);
+      n2 += xor32(n2);
+      v *= 1.0f / (float)m.us;  // a whole unit has us tokens at least
+      const bool there = blk * m.us < Lend;
+      n2 = there ? (n2 < INFINITY ? n2 : INFINITY) : 0.f;
+      v = there ? (fine ? v : INFINITY) : 0.f;
+      n2 = wave_max(n2);
+      v = wave_max(v);
+      if (lane == 0) unit_max[((int64_t)bh * m.n_tiles + tile) * 4 + w] = make_float2(n2, v);
+    }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       float f[8];
@@ -318,17 +351,26 @@ __global__ __launch_bounds__(256, 2) void prefill_score_kernel(
       uint4 raw[KS];
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) raw[ks] = *reinterpret_cast<const uint4*>(qr + 32 * ks);
+      float n2 = 0.f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const bf16x8 v = __builtin_bit_cast(bf16x8, raw[ks]);
         float f[8];
         bf16x8 hi, lo;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] = (float)v[e] * (float)v[e];
+        for (int e = 0; e < 8; ++e) {
+          f[e] = (float)v[e] * (float)v[e];
+          n2 += f[e];
+        }
         split_bf16x8(f, hi, lo);
         sm.q[w][ks][lane] = raw[ks];
         sm.q2h[w][ks][lane] = __builtin_bit_cast(uint4, hi);
         sm.q2l[w][ks][lane] = __builtin_bit_cast(uint4, lo);
+      }
+      if (tile == 0) {  // uniform
+        n2 += xor16(n2);
+        n2 += xor32(n2);
+        if (ok && lg == 0) q_norm2[(int64_t)bh * R + r] = n2;
       }
     }
     __syncthreads();
@@ -428,20 +470,31 @@ __global__ __launch_bounds__(256, 2) void prefill_score_kernel(
 
 // ----------------------------------------------------------- selection
 // The decode's selection, per query; a query whose blocks all fit in k needs
-// no scores. A query whose cutoff separates two scores closer than kTieSpan
+// no scores. A query whose cutoff separates two scores closer than its tie_span
 // is not selected but put on a list: prefill_rescore_kernel takes its block
 // masses again with the decode's arithmetic, and a second launch of this
 // kernel selects the listed queries from those, so that what the rounding of
-// the scoring kernel could decide is decided as the decode decides it (about
-// four of 8192 independent queries over 2048 blocks are listed; without it
-// four in a million selected another block than the decode, none in two
-// million with it).
+// the scoring kernel could decide is decided as the decode decides it.
 // SWN: tile weights (tiles x heads) in LDS, sized to the shape so that several
 // workgroups share a compute unit. Past 32 queries per compute unit each
 // workgroup takes a run of them (one per query spends 14 us per 16000 queries
 // on starting workgroups alone, which is most of it where every block is
 // selected).
-constexpr float kTieSpan = 1e-6f;  // relative; the two roundings differ by about 1e-8
+//
+// The span. With u = 2^-24, mean mu and variance v of a unit and x = s^2 <q^2, v>
+// / 2, the two scorings' log masses differ by the rounding of their partial sums
+// of s q . mu, at most u s |q| |mu| or so, and of the logarithms of n and 1 + x.
+// Measured over 11 million units (d = 64 and 128, blocks and windows, means of
+// up to 4700 = s |q| |mu|, x of up to e^11): at most 0.91 u (s |q| |mu| + 4 ln(1 +
+// x) + 4), and this scoring no further from 64 bits than the decode's. That much
+// (0.91 taken as 1, with the largest |mu| and v of the sequence and KV head) can
+// move a mass and its head's normaliser, of each of the two scores. (Atomic maxima
+// in place of a maximum per tile, reduced here, took the scoring of 8192 windows
+// from 156 to 257 us.)
+__device__ __forceinline__ float tie_span(float s, float q_norm2, float mu_norm2, float var) {
+  const float ln = __builtin_amdgcn_logf(1.0f + 0.5f * s * s * q_norm2 * var) * kLn2f32;
+  return fminf(1.0f, 0x1p-22f * (s * sqrtf(q_norm2 * mu_norm2) + 4.0f * ln + 4.0f));
+}
 
 struct PrefSelectArgs {
   Dims m;
@@ -450,15 +503,19 @@ struct PrefSelectArgs {
   const float* e_vals;
   const double* tile_part;
   int32_t *sel_ws, *sel_out;
-  int32_t* near;  // [bh]: listed queries of each (sequence, KV head); the longest list;
-                  // [bh][T]: their positions
-  int listed;     // select the listed queries (else every query, listing some)
+  int32_t* near;           // NearLists
+  const float2* unit_max;  // largest |mean|^2 and variance of each 16 units
+  const float* q_norm2;    // |q|^2 per query row
+  float s;
+  int listed;  // select the listed queries (else every query, listing some)
 };
 
 template <int R, bool WIN, int NT, int SWN, int GMAX>
 __global__ __launch_bounds__(NT) void prefill_select_kernel(PrefSelectArgs a) {
   __shared__ SelectSmem<NT, SWN> sm;
   __shared__ float wsc[WIN ? kMaxWindows : 1];
+  __shared__ float2 s_um;  // (in LDS, as the span is: registers are short in the selection)
+  __shared__ float s_span;
   const Dims& m = a.m;
   auto length = [&](int vh) {
     int L0, nv;
@@ -468,10 +525,10 @@ __global__ __launch_bounds__(NT) void prefill_select_kernel(PrefSelectArgs a) {
   // this workgroup's queries: a run of them, those whose blocks all fit in k
   // first, as one run of stores; or every gridDim.x-th entry of the lists, entry
   // x / bh of the list of x % bh (short lists spread over the workgroups)
-  int32_t* list = a.near + m.bh + 1;
+  const NearLists nl = near_lists(m, a.near);
   const int n_q = m.bh * a.T, per = (n_q - 1) / (int)gridDim.x + 1;
   const int x0 = a.listed ? (int)blockIdx.x : (int)blockIdx.x * per;
-  const int x1 = a.listed ? m.bh * a.near[m.bh] : min(x0 + per, n_q);
+  const int x1 = a.listed ? m.bh * *nl.longest : min(x0 + per, n_q);
   const int step = a.listed ? (int)gridDim.x : 1;
   if (x0 >= x1) return;
   if (!a.listed && per > 1) {
@@ -486,22 +543,41 @@ __global__ __launch_bounds__(NT) void prefill_select_kernel(PrefSelectArgs a) {
     // (lengths grow along a run of one (sequence, KV head))
     if (x0 / a.T == (x1 - 1) / a.T && (length(x1 - 1) + m.B - 1) / m.B <= m.k) return;
   }
+  int bh_max = -1;  // (sequence, KV head) whose largest |mean|^2 and variance s_um holds
   for (int x = x0; x < x1; x += step) {
     int vh = x;
     if (a.listed) {
-      if (x / m.bh >= a.near[x % m.bh]) continue;  // uniform
-      vh = x % m.bh * a.T + list[(int64_t)(x % m.bh) * a.T + x / m.bh];
+      if (x / m.bh >= nl.count[x % m.bh]) continue;  // uniform
+      vh = x % m.bh * a.T + nl.list[(int64_t)(x % m.bh) * a.T + x / m.bh];
     }
     const int bh = vh / a.T, i = vh % a.T, L = length(vh);
     if (!a.listed && per > 1 && (L + m.B - 1) / m.B <= m.k) continue;  // uniform; written above
+    float span = 0.f;
+    if (!a.listed && (L + m.B - 1) / m.B > m.k) {  // uniform
+      if (bh != bh_max) {
+        int L0, nv;
+        chunk_bounds(m, a.seq_lens, bh / m.hkv, a.T, &L0, &nv);
+        const int n16 = ((L0 + nv - 1) / m.us / kTileBlocks + 1) * 4;  // of the tiles scored
+        float2 um = make_float2(0.f, 0.f);
+        for (int t = threadIdx.x & 63; t < n16; t += 64) {
+          const float2 v = a.unit_max[(int64_t)bh * m.n_tiles * 4 + t];
+          um = make_float2(fmaxf(um.x, v.x), fmaxf(um.y, v.y));
+        }
+        s_um = make_float2(wave_max(um.x), wave_max(um.y));  // the same in every wavefront
+        bh_max = bh;
+      }
+      float n2 = 0.f;
+      for (int g = 0; g < m.group; ++g) n2 = fmaxf(n2, a.q_norm2[(int64_t)vh * m.group + g]);
+      span = tie_span(a.s, n2, s_um.x, s_um.y);
+    }
+    s_span = span;  // the same in every thread, here and before barriers in the selection
     const bool near = select_blocks<NT, R, SWN, false, 0, WIN, GMAX, false, true>(
         m, vh, L, a.e_vals, a.tile_part, sm, a.sel_ws + (int64_t)vh * m.k, nullptr,
-        a.sel_out ? a.sel_out + ((int64_t)i * m.bh + bh) * m.k : nullptr, wsc,
-        a.listed ? 0.f : kTieSpan);
+        a.sel_out ? a.sel_out + ((int64_t)i * m.bh + bh) * m.k : nullptr, wsc, &s_span);
     if (near && threadIdx.x == 0) {
-      const int j = atomicAdd(a.near + bh, 1);
-      list[(int64_t)bh * a.T + j] = i;
-      atomicMax(a.near + m.bh, j + 1);
+      const int j = atomicAdd(nl.count + bh, 1);
+      nl.list[(int64_t)bh * a.T + j] = i;
+      atomicMax(nl.longest, j + 1);
     }
     __syncthreads();  // the next query's selection writes the same LDS
   }
@@ -523,19 +599,20 @@ template <int D>
 __global__ __launch_bounds__(256, 2) void prefill_rescore_kernel(
     Dims m, int T_, int W, const float* __restrict__ stats, const int32_t* __restrict__ seq_lens,
     const bf16_t* __restrict__ q, double s, int first_order, const double* __restrict__ ell_part,
-    const int32_t* __restrict__ near, float* __restrict__ e_vals, double* __restrict__ tile_part) {
+    int32_t* __restrict__ near, float* __restrict__ e_vals, double* __restrict__ tile_part) {
   constexpr int NK = D / 4, NQ = D / 32;  // k-steps, partials per quarter of the coordinates
   __shared__ float s_c[2][NK][64];        // s q and s^2 q^2 / 2, as operands
   __shared__ double s_mx[4][16], s_sum[4][16];
   const int G = m.group, kP = 16 / G, nbp = m.n_tiles * kTileBlocks;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int li = lane & 15, lg = lane >> 4;
-  const int tile = blockIdx.x, bh = blockIdx.z, n_near = near[bh];
+  const NearLists nl = near_lists(m, near);
+  const int tile = blockIdx.x, bh = blockIdx.z, n_near = nl.count[bh];
   if ((int)blockIdx.y * kP >= n_near) return;
   int L0, nv;
   chunk_bounds(m, seq_lens, bh / m.hkv, T_, &L0, &nv);
   if (tile * kTileBlocks * m.us >= L0 + nv) return;  // past every query's tokens
-  const int32_t* list = near + m.bh + 1 + (int64_t)bh * T_;
+  const int32_t* list = nl.list + (int64_t)bh * T_;
   float pm[NK], pv[NK];
   {
     const float* st = stats + stats_off4(m, bh, (int64_t)tile * kTileBlocks, 0, 0);  // uniform
@@ -1213,7 +1290,8 @@ static hipError_t prefill_chunk_d(const Dims& m, const spla_config& cfg, const s
                      dim3(256), 0, st, m, T, W, (const float*)c.blk_stats,
                      (const int32_t*)c.seq_lens, q, s_score, fo,
                      (const double*)(base + ws.ell_part), (float*)(base + ws.e_vals),
-                     (double*)(base + ws.tile_part));
+                     (double*)(base + ws.tile_part), (float2*)(base + ws.unit_max),
+                     (float*)(base + ws.q_norm2));
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark_phase(ev, SPLA_PHASE_SCORE, true, st);
   // 4. selection of every query: without windows and up to 2048 blocks, 256
@@ -1231,6 +1309,9 @@ static hipError_t prefill_chunk_d(const Dims& m, const spla_config& cfg, const s
   sa.sel_ws = (int32_t*)(base + ws.sel);
   sa.sel_out = sel_out;
   sa.near = (int32_t*)(base + ws.near);
+  sa.unit_max = (const float2*)(base + ws.unit_max);
+  sa.q_norm2 = (const float*)(base + ws.q_norm2);
+  sa.s = (float)s_score;
   sa.listed = 0;
   auto select = [&](auto f) {
     f(sa, st);

@@ -273,6 +273,9 @@ struct PrefillWs {
   int64_t sel;        // i32 [bh T][k]
   int64_t near;       // i32 [bh], 1, [bh][T]  queries whose selection is taken again: count per
                       //   (sequence, KV head), the largest count, their positions
+  int64_t unit_max;   // f32 [bh][n_tiles][4][2]  what decides which: the largest |mean|^2 and
+                      //   variance of each 16 units
+  int64_t q_norm2;    // f32 [bh][T G]  ... and |q|^2 per query row
   int64_t part_s;     // f32 [bh][n_blk][d][d]  phi(K)^T V of each block the chunk touches
   int64_t part_z;     // f32 [bh][n_blk][d]
   int64_t s_hi, s_lo; // bf16 [bh][n_blk][d d]  S_bar before each block, operand order
@@ -303,6 +306,8 @@ SPLA_HD PrefillWs prefill_ws_layout(const Dims& m, int n_tokens) {
   w.tile_part = take(nq * m.n_tiles * m.group * 2 * 8);
   w.sel = take(nq * m.k * 4);
   w.near = take((m.bh + 1 + nq) * 4);
+  w.unit_max = take((int64_t)m.bh * m.n_tiles * 4 * 2 * 4);
+  w.q_norm2 = take(nq * m.group * 4);
   w.part_s = take(nb * m.d * m.d * 4);
   w.part_z = take(nb * m.d * 4);
   w.s_hi = take(nb * m.d * m.d * 2);

@@ -206,19 +206,19 @@ __device__ __forceinline__ void radix_cut(const uint32_t (&key)[R], uint32_t kp,
 // at most eight heads and eight blocks per thread every head's masses load
 // in one batch, and a wavefront that takes a second head's tile partials
 // loads them with the first head's. GEX: the group is GMAX exactly.
-// near_span > 0: where the cutoff separates two scores closer than near_span
+// LOOP: for a workgroup that selects several queries in turn. Where near (LDS)
+// holds a span > 0 and the cutoff separates two scores closer than that
 // (relative), nothing is written and the result is true (in every thread);
-// otherwise it is false. LOOP: for a workgroup that selects several queries in
-// turn; the thread's index is opaque, so that the addresses and masks it gives
-// are formed anew each time (kept over the loop they took up to 105 registers
-// more, and up to 125 spilled at 1024 threads).
+// otherwise it is false. And the thread's index is opaque, so that the addresses
+// and masks it gives are formed anew each time (kept over the loop they took up
+// to 105 registers more, and up to 125 spilled at 1024 threads).
 template <int NT, int R, int SWN, bool CO, int SEL_OFF = 0, bool WIN = false,
           int GMAX = SPLA_MAX_GROUP, bool GEX = false, bool LOOP = false>
 __device__ bool select_blocks(const Dims& m, int bh, int seq_len,
                               const float* __restrict__ e_vals,
                               const double* __restrict__ tile_part, SelectSmem<NT, SWN>& sm,
                               int32_t* sel, int32_t* meta4, int32_t* so,
-                              float* wsc = nullptr, float near_span = 0.f) {
+                              float* wsc = nullptr, const float* near = nullptr) {
   constexpr int NW = NT / 64;
   constexpr int HC0 = R <= 2 ? 16 / R : (R <= 8 ? 4 : 32 / R);
   constexpr int HC = (R <= 8 && GMAX <= 8 && GMAX > HC0) ? GMAX : HC0;  // heads per load batch
@@ -477,6 +477,7 @@ __device__ bool select_blocks(const Dims& m, int bh, int seq_len,
     }
   }
 
+  const float near_span = LOOP ? *near : 0.f;
   if (near_span > 0.f && kp > 0) {  // uniform
     // the smallest score taken and the largest one left out (keys are a
     // score's bits + 1; a score is never negative)
@@ -500,7 +501,7 @@ __device__ bool select_blocks(const Dims& m, int bh, int seq_len,
       lo = fminf(lo, __uint_as_float(sm.bits[0][x]));
       hi = fmaxf(hi, __uint_as_float(sm.bits[1][x]));
     }
-    if (hi >= lo * (1.0f - near_span)) return true;
+    if (!(hi < lo * (1.0f - near_span))) return true;  // (also where a score is NaN)
     __syncthreads();  // bits is written again below
   }
 

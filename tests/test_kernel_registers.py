@@ -62,8 +62,8 @@ def kernels():
     (r"prefill_select_kernel<\d+, false, 256,", 0, 128),
     # 1024 threads leave 128 registers; 32 blocks, or 16 windows, per thread fill them
     (r"prefill_select_kernel<(4|8|16), false, 1024,", 0, 128),
-    (r"prefill_select_kernel<32, false, 1024,", 4, 128),
-    (r"prefill_select_kernel<\d+, true, 1024,", 20, 128),
+    (r"prefill_select_kernel<32, false, 1024,", 8, 128),
+    (r"prefill_select_kernel<\d+, true, 1024,", 24, 128),
     (r"prefill_group_kernel<", 0, 256),
     # up to 2048 blocks: the step and the three-wave decode; the four-wave decode
     (r"decode_kernel<[1-6], \d+, 8, (true|false), 3,", 0, 168),
