@@ -203,8 +203,7 @@ enum {
  * prefill (spla_prefill_ex) records APPEND (the units in progress, the rows
  * and the statistics of the chunk), LINEAR, SCORE, SELECT, SPARSE and MERGE
  * (empty unless groups are split) for every chunk, so with several chunks the
- * events end up
- * bracketing the last one. */
+ * events end up bracketing the last one. */
 typedef struct spla_events {
   void* start[SPLA_NUM_PHASES];
   void* stop[SPLA_NUM_PHASES];
@@ -248,7 +247,8 @@ int32_t spla_append_workspace_bytes(const spla_config* cfg, int32_t max_new, siz
 /* Device workspace that spla_prefill needs for n_tokens positions per
  * sequence (host-only query): per-query scores, selections and records and the
  * global terms of one chunk for the chunked shapes, the decode workspace for
- * the others. It grows with n_tokens. */
+ * the others. It grows with n_tokens, for the chunked shapes up to 320 MB or
+ * what 32 positions need, whichever is more. */
 int32_t spla_prefill_workspace_bytes(const spla_config* cfg, int32_t n_tokens,
                                      size_t* out_bytes);
 
@@ -343,15 +343,15 @@ int32_t spla_step(const spla_config* cfg, const spla_cache* cache, const void* k
  *  workspace:    at least spla_prefill_workspace_bytes(cfg, n_tokens) bytes,
  *                256-byte aligned (no preparation needed).
  * bf16 shapes with G <= 8 run chunks of up to 1024 positions (as many as keep
- * the chunk's block scores within 320 MB, at least 32) through the chunked
- * kernels (Sec. 3.3 "Kernel Design": the global linear term from S_bar before
- * each block of the chunk, block scores of every query on the matrix cores,
- * per-query top-k, and the fused sparse kernel over groups of consecutive
- * queries, which share the blocks that more than one of them selects); other
- * shapes (which never decode in one launch) run the positions one at a time as
- * spla_step does, on the separate decode launches. n_tokens = 0 does nothing;
- * tokens past max_seq_len are dropped as in spla_step (SPLA_DEVERR_CAPACITY) and the queries at those
- * positions decode over the full cache. */
+ * the workspace within 320 MB, at least 32) through the chunked kernels (Sec.
+ * 3.3 "Kernel Design": the global linear term from S_bar before each block of
+ * the chunk, block scores of every query on the matrix cores, per-query top-k,
+ * and the fused sparse kernel over groups of consecutive queries, which share
+ * the blocks that more than one of them selects); other shapes (which never
+ * decode in one launch) run the positions one at a time as spla_step does, on
+ * the separate decode launches. n_tokens = 0 does nothing; tokens past
+ * max_seq_len are dropped as in spla_step (SPLA_DEVERR_CAPACITY) and the
+ * queries at those positions decode over the full cache. */
 int32_t spla_prefill(const spla_config* cfg, const spla_cache* cache, int32_t n_tokens,
                      const void* k_new, const void* v_new, const void* q,
                      const float* rms_weight, void* out, int32_t* sel_idx, void* workspace,

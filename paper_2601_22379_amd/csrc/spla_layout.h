@@ -226,16 +226,16 @@ SPLA_HD int step_pre(const Dims& m) {
 SPLA_HD bool step_fusable(const Dims& m) { return use_mfma_sparse(m) && step_pre(m) <= kStepPre; }
 
 // ---- chunked prefill workspace ------------------------------------------------
-// Positions per chunk: as many as keep the block masses of the chunk's queries
-// (e_vals) within kPrefillScoreBytes, between kPrefillMinChunk and
-// kPrefillMaxChunk. Long chunks fill the GPU (a chunk's launches take a few
-// microseconds each whatever it holds: 1000 positions of 4 x 8 units from an
-// empty cache took 233 us in two chunks against 4430 us in chunks of 32). At
-// 128K tokens and 4 x 8 units the limit gives chunks of 320 positions (256
-// positions in one chunk rather than two of 128 also saves the split groups'
-// records).
+// Positions per chunk: as many as keep the whole workspace within kPrefillBytes,
+// between kPrefillMinChunk and kPrefillMaxChunk. Long chunks fill the GPU (a
+// chunk's launches take a few microseconds each whatever it holds: 1000 positions
+// of 4 x 8 units from an empty cache took 233 us in two chunks, 4430 us in chunks
+// of 32). At 128K tokens and 4 x 8 units the limit gives chunks of 288 positions,
+// the block masses of whose queries are most of it; with many heads and short
+// sequences it is the state before each block (64 KB per block and unit at d =
+// 128: 64 x 8 units of B = 32 run chunks of 97).
 constexpr int kPrefillMinChunk = 32, kPrefillMaxChunk = 1024;
-constexpr int64_t kPrefillScoreBytes = 320 << 20;
+constexpr int64_t kPrefillBytes = 320 << 20;
 constexpr int kPrefillFill = 512;   // group-pass workgroups to aim for (two per compute unit)
 constexpr int kPrefillMaxSplit = 16;  // workgroups that share one group's blocks at most
 
@@ -264,67 +264,77 @@ SPLA_HD int prefill_splits(const Dims& m, int T) {
   return (int)(n < kPrefillMaxSplit ? n : kPrefillMaxSplit);
 }
 
+// part_s and part_z, then e_vals to q_norm2, then part lie over one another: each
+// group is written after the one before it was last read (one stream).
 struct PrefillWs {
   int T;            // positions per chunk at most
   int part_stride;  // floats per record
   int64_t ell_part;   // f64 [bh][T][W][G]  log masses of the units in progress (W = ul / us)
-  int64_t e_vals;     // f32 [bh][T G][n_tiles*64]  per query row, as the decode's
-  int64_t tile_part;  // f64 [bh][T G][n_tiles][2]
   int64_t sel;        // i32 [bh T][k]
   int64_t near;       // i32 [bh], 1, [bh][T]  queries whose selection is taken again: count per
                       //   (sequence, KV head), the largest count, their positions
-  int64_t unit_max;   // f32 [bh][n_tiles][4][2]  what decides which: the largest |mean|^2 and
-                      //   variance of each 16 units
-  int64_t q_norm2;    // f32 [bh][T G]  ... and |q|^2 per query row
-  int64_t part_s;     // f32 [bh][n_blk][d][d]  phi(K)^T V of each block the chunk touches
-  int64_t part_z;     // f32 [bh][n_blk][d]
   int64_t s_hi, s_lo; // bf16 [bh][n_blk][d d]  S_bar before each block, operand order
   int64_t z_pre;      // f32 [bh][n_blk][d]
+  int64_t part_s;     // f32 [bh][n_blk][d][d]  phi(K)^T V of each block the chunk touches
+  int64_t part_z;     // f32 [bh][n_blk][d]
+  int64_t e_vals;     // f32 [bh][T G][n_tiles*64]  per query row, as the decode's
+  int64_t tile_part;  // f64 [bh][T G][n_tiles][2]
+  int64_t unit_max;   // f32 [bh][n_tiles][4][2]  the largest |mean|^2 and variance of each 16 units
+  int64_t q_norm2;    // f32 [bh][T G]  |q|^2 per query row
   int64_t part;       // f32 [bh T][n_split][part_stride]  records of split groups
   int64_t total;
 };
 
-// Every size grows with n_tokens, so a workspace for n positions serves every
-// smaller call.
-SPLA_HD PrefillWs prefill_ws_layout(const Dims& m, int n_tokens) {
+// The workspace of chunks of up to T positions; every size grows with T.
+SPLA_HD PrefillWs prefill_chunk_layout(const Dims& m, int T) {
   PrefillWs w;
-  const int64_t A = SPLA_WORKSPACE_ALIGN;
   int64_t off = 0;
   auto take = [&](int64_t bytes) {
-    int64_t o = off;
-    off = align_up(off + bytes, A);
+    const int64_t o = off;
+    off = align_up(off + bytes, SPLA_WORKSPACE_ALIGN);
     return o;
   };
-  const int64_t row = (int64_t)m.bh * m.group * m.n_tiles * kTileBlocks * 4;  // e_vals per position
-  int64_t T = kPrefillScoreBytes / row;
-  T = T < kPrefillMinChunk ? kPrefillMinChunk : (T > kPrefillMaxChunk ? kPrefillMaxChunk : T);
-  w.T = (int)(n_tokens < 1 ? 1 : (n_tokens < T ? n_tokens : T));
+  w.T = T;
   w.part_stride = kPartHead + 2 * m.group * m.d;
-  const int64_t nq = (int64_t)m.bh * w.T, nb = (int64_t)m.bh * prefill_blocks(m, w.T);
+  const int64_t nq = (int64_t)m.bh * T, nb = (int64_t)m.bh * prefill_blocks(m, T);
   w.ell_part = take(nq * (m.ul / m.us) * m.group * 8);
-  w.e_vals = take(row * w.T);
-  w.tile_part = take(nq * m.n_tiles * m.group * 2 * 8);
   w.sel = take(nq * m.k * 4);
   w.near = take((m.bh + 1 + nq) * 4);
-  w.unit_max = take((int64_t)m.bh * m.n_tiles * 4 * 2 * 4);
-  w.q_norm2 = take(nq * m.group * 4);
-  w.part_s = take(nb * m.d * m.d * 4);
-  w.part_z = take(nb * m.d * 4);
   w.s_hi = take(nb * m.d * m.d * 2);
   w.s_lo = take(nb * m.d * m.d * 2);
   w.z_pre = take(nb * m.d * 4);
-  // records: T n_split(T) per (sequence, KV head), at most T times the largest
-  // split and at most T + kPrefillFill (positions per group) / bh (n_split <
-  // kPrefillFill / groups + 1, groups >= bh T / positions); none when no
-  // smaller chunk splits either
-  const int64_t qw = 4 * prefill_wave_positions(m.group);
-  const int64_t by_fill = w.T + ceil_div(kPrefillFill * qw, m.bh);
-  const int64_t by_split = (int64_t)w.T * kPrefillMaxSplit;
-  const bool splits = prefill_splits(m, 1) > 1;
-  w.part = take(splits ? (int64_t)m.bh * (by_fill < by_split ? by_fill : by_split) * w.part_stride * 4
-                       : 0);
+  const int64_t base = off;
+  w.part_s = take(nb * m.d * m.d * 4);
+  w.part_z = take(nb * m.d * 4);
   w.total = off;
+  off = base;
+  w.e_vals = take(nq * m.group * m.n_tiles * kTileBlocks * 4);
+  w.tile_part = take(nq * m.n_tiles * m.group * 2 * 8);
+  w.unit_max = take((int64_t)m.bh * m.n_tiles * 4 * 2 * 4);
+  w.q_norm2 = take(nq * m.group * 4);
+  w.total = w.total > off ? w.total : off;
+  off = base;
+  // records: the most that a chunk of t <= T positions splits into, t
+  // n_split(t) per (sequence, KV head): n_split is largest for one position,
+  // below kPrefillFill / groups + 1, and 1 from F = kPrefillFill (positions per
+  // group) / bh positions on (groups >= bh t / positions per group)
+  const int64_t F = ceil_div(kPrefillFill * 4 * prefill_wave_positions(m.group), m.bh);
+  const int64_t n1 = prefill_splits(m, 1), t = T < F ? T : F;
+  const int64_t rows = n1 > 1 ? (t * n1 < t + F ? t * n1 : t + F) : 0;
+  w.part = take(m.bh * rows * w.part_stride * 4);
+  w.total = w.total > off ? w.total : off;
   return w;
+}
+
+// A workspace for n_tokens positions serves every smaller call.
+SPLA_HD PrefillWs prefill_ws_layout(const Dims& m, int n_tokens) {
+  int lo = kPrefillMinChunk, hi = kPrefillMaxChunk;  // the largest chunk within the limit
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (prefill_chunk_layout(m, mid).total <= kPrefillBytes) lo = mid;
+    else hi = mid - 1;
+  }
+  return prefill_chunk_layout(m, n_tokens < 1 ? 1 : (n_tokens < lo ? n_tokens : lo));
 }
 
 // ---- append workspace ------------------------------------------------------

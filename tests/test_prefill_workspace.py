@@ -1,0 +1,44 @@
+"""Size of the chunked prefill's workspace: within 320 MB, or what 32 positions need,
+whichever is more, and room for the records of every chunk that a call can split
+into."""
+
+import pytest
+
+from paper_2601_22379_amd import spla
+
+SHAPES = [  # batch, KV heads, group, d, B, k, capacity
+    (4, 8, 4, 128, 64, 16, 32768), (64, 8, 1, 128, 32, 16, 2048), (64, 8, 4, 128, 32, 16, 2048),
+    (4, 8, 4, 128, 64, 32, 131072), (64, 8, 4, 128, 128, 16, 65536), (1, 1, 1, 64, 32, 8, 1 << 20),
+    (2, 2, 8, 128, 32, 256, 8192), (16, 8, 8, 128, 128, 64, 8192)]
+
+
+def size(shape, n):
+    b, hkv, g, d, B, k, cap = shape
+    cfg = spla.make_config(b, hkv * g, hkv, d, B, k, cap)
+    return spla.prefill_workspace_bytes(cfg, n, library=spla.host_lib())
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_bounded(shape):
+    least = size(shape, min(32, shape[-1]))
+    for n in (100, 1000, 1024, 2048):
+        assert size(shape, min(n, shape[-1])) <= max(320 << 20, least)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_records_fit(shape):
+    """Rows of records a chunk of t positions writes (t per split of its groups), by
+    the rule that sets the number of splits, against what the buffer for T holds."""
+    b, hkv, g, d, B, k, cap = shape
+    bh, qw = b * hkv, 4 * (16 if g <= 1 else 8 if g <= 2 else 4 if g <= 4 else 2)
+
+    def splits(t):
+        groups = bh * ((t + qw - 2) // qw + 1)
+        return min(-(-512 // groups), -(-k * (B // 32) // 4), 16)
+
+    row = (48 + 2 * g * d) * 4
+    for T in (1, 2, 7, 31, 32, 33, 64, 100, 256, 1000):
+        if T > cap:
+            continue
+        need = max(t * splits(t) if splits(t) > 1 else 0 for t in range(1, T + 1))
+        assert bh * need * row <= size(shape, T)
