@@ -2,10 +2,10 @@
 
 T tokens per sequence are prefilled; the query at position L_b + t must
 match the oracle's decode over the first L_b + t + 1 tokens (the oracle
-prefill). bf16 shapes with G <= 8 run the chunked kernels (chunks of up to
-32 positions); the fp32 case runs position by position. The cases cross
-block and window boundaries, span several chunks, start from an empty
-cache, run into the capacity, use a paged pool and every variant flag.
+prefill). bf16 shapes with G <= 8 run the chunked kernels (each call here is
+one chunk); the fp32 case runs position by position. The cases cross block and
+window boundaries, start from an empty cache, run into the capacity, use a
+paged pool and every variant flag.
 """
 
 import numpy as np
@@ -41,7 +41,7 @@ CASES = {
     "bf16_strided": (dict(batch=1, n_q_heads=8, n_kv_heads=2, head_dim=128, block_size=64,
                           top_k=8, lengths=[2040], capacity=2112, kind="iid"),
                      dict(sel_window=32, sel_stride=16), 12),
-    # three chunks (32 + 32 + 6), G = 8, B = 32: chunks cross several blocks
+    # G = 8, B = 32: 70 positions cross several blocks
     "bf16_g8_B32_chunks": (dict(batch=2, n_q_heads=16, n_kv_heads=2, head_dim=128, block_size=32,
                                 top_k=10, lengths=[300, 1500], capacity=1600,
                                 kind="pareto_planted", n_planted=3), {}, 70),
@@ -49,7 +49,7 @@ CASES = {
     "bf16_d64_B128_empty": (dict(batch=2, n_q_heads=4, n_kv_heads=2, head_dim=64, block_size=128,
                                  top_k=3, lengths=[0, 600], capacity=1024, kind="drift",
                                  n_sink=1, n_local=1), {}, 40),
-    # strided windows over two chunks, G = 6
+    # strided windows, G = 6
     "bf16_g6_strided_chunks": (dict(batch=2, n_q_heads=12, n_kv_heads=2, head_dim=128,
                                     block_size=64, top_k=8, lengths=[1500, 777], capacity=2048,
                                     kind="block_offsets"),
