@@ -461,6 +461,9 @@ __device__ __forceinline__ void step_load(const Dims& m, const bf16_t* __restric
   in.vc = bf16_to_f32(v_step[(int64_t)bh * D + tid % D].bits);
 }
 
+// Shapes that hold more than kSparsePre entries take the exponentials as
+// append_rank1_rows does, whose update of S_bar this replaces there: their state
+// is the same bits whichever of the two makes a step.
 template <int D, int PRE>
 __device__ __forceinline__ void step_apply(const Dims& m, StepIn<D>& in, float* S, float* zbar,
                                            int bh, SparseRegs<PRE>& r) {
@@ -473,7 +476,8 @@ __device__ __forceinline__ void step_apply(const Dims& m, StepIn<D>& in, float* 
   float sum = 0.f;
 #pragma unroll
   for (int e = 0; e < D / 64; ++e) {
-    in.x[e] = expf(in.x[e] - mx);
+    in.x[e] = PRE > kSparsePre ? __builtin_amdgcn_exp2f(fmaf(in.x[e], kLog2e, -mx * kLog2e))
+                               : expf(in.x[e] - mx);
     sum += in.x[e];
   }
   sum = wave_sum(sum);
