@@ -1152,9 +1152,14 @@ __global__ __launch_bounds__(256, 2) void prefill_group_kernel(GroupArgs a) {
     group_start<D, false>(a, bh, xw, s, sm);
     group_walk<D, BLK, false, false>(a, bh, s, sm);
   }
-  if (group_not_finite<D>(s)) {  // (without the linear branch al is not used)
-    group_start<D, true>(a, bh, xw, s, sm);
-    group_walk<D, BLK, true, true>(a, bh, s, sm);
+  if (group_not_finite<D>(s)) {
+    if (lin) {
+      group_start<D, true>(a, bh, xw, s, sm);
+      group_walk<D, BLK, true, true>(a, bh, s, sm);
+    } else {
+      group_start<D, false>(a, bh, xw, s, sm);
+      group_walk<D, BLK, false, true>(a, bh, s, sm);
+    }
   }
   auto& ax = s.ax;
   auto& al = s.al;
