@@ -126,7 +126,8 @@ struct DecodeWs {
   int64_t sel;        // i32 [bh][k]               selected blocks, ascending
   int64_t meta;       // i32 [bh][4]               (n_selected, all_selected, length, 0)
   int64_t part;       // f32 [bh][n_wg][part_stride]  sparse workgroup partials
-  int64_t appended;   // i32 [batch]               tokens a step appended (fused step)
+  int64_t appended;   // i32 [batch]               tokens a step appended: written by the
+                      //   single-token append, read by the sparse pass of separate launches
   int64_t cand_key;   // u32 [bh][n_sl][k]         two-stage selection: slice candidates' keys
   int64_t cand_id;    // i32 [bh][n_sl][k]         ... their block ids (ascending per slice)
   int64_t cand_n;     // i32 [bh][n_sl]            ... their count per slice

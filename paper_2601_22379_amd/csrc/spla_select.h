@@ -143,50 +143,6 @@ struct SelectSmem {
   int32_t out[SPLA_MAX_TOP_K + 1];
 };
 
-// The kp-th largest of the keys held R per thread by the NT threads (0: not
-// a candidate), found digit by digit as in select_blocks: keys above gt are
-// taken and, of the keys equal to eqv, the first eq_need in thread order.
-// Fewer than kp candidates: every candidate (gt = 0). hist: 4096 words,
-// zeroed by the caller before a barrier.
-template <int NT, int R>
-__device__ __forceinline__ void radix_cut(const uint32_t (&key)[R], uint32_t kp, uint32_t* hist,
-                                          uint32_t& gt, uint32_t& eqv, uint32_t& eq_need) {
-  const int lane = threadIdx.x & 63;
-  gt = 0xFFFFFFFFu;
-  eqv = 0u;
-  eq_need = 0u;
-  uint32_t prefix = 0u, need = kp;
-#pragma unroll
-  for (int rd = 0; rd < 3; ++rd) {
-    const int sh = 20 - 10 * rd;
-    const uint32_t msk = rd == 0 ? 0x7FFu : 0x3FFu;
-    uint32_t* H = hist + (rd == 0 ? 0 : 1024 + 1024 * rd);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const bool in = (key[r] != 0u) & ((rd == 0) | ((key[r] >> (sh + 10)) == prefix));
-      if (__ballot(in) != 0ull) atomicAdd(&H[(key[r] >> sh) & msk], in ? 1u : 0u);
-    }
-    __syncthreads();
-    const RadixPick p = rd == 0 ? radix_pick<32>(H, need, lane) : radix_pick<16>(H, need, lane);
-    if (rd == 0 && p.total < need) {
-      gt = 0u;
-      return;
-    }
-    need -= p.above;
-    prefix = (prefix << 10) | p.digit;
-    if (need == p.cnt) {
-      const uint32_t lo = prefix << sh;
-      gt = lo == 0u ? 0u : lo - 1u;
-      return;
-    }
-    if (rd == 2) {
-      gt = prefix;
-      eqv = prefix;
-      eq_need = need;
-    }
-  }
-}
-
 // The selection of sequence x KV head bh (length seq_len, clipped to the
 // capacity) by the NT threads of a workgroup, thread t owning blocks
 // t R .. t R + R - 1 (NT R >= blocks of the capacity). The length is an
@@ -600,6 +556,50 @@ __device__ bool select_blocks(const Dims& m, int bh, int seq_len,
 constexpr int kSliceThreads = 256;
 constexpr int kSliceR = kSliceBlocks / kSliceThreads;     // blocks per thread
 constexpr int kSliceTiles = kSliceBlocks / kTileBlocks;   // 16 statistics tiles
+
+// The kp-th largest of the keys held R per thread by the NT threads (0: not
+// a candidate), found digit by digit as in select_blocks: keys above gt are
+// taken and, of the keys equal to eqv, the first eq_need in thread order.
+// Fewer than kp candidates: every candidate (gt = 0). hist: 4096 words,
+// zeroed by the caller before a barrier.
+template <int NT, int R>
+__device__ __forceinline__ void radix_cut(const uint32_t (&key)[R], uint32_t kp, uint32_t* hist,
+                                          uint32_t& gt, uint32_t& eqv, uint32_t& eq_need) {
+  const int lane = threadIdx.x & 63;
+  gt = 0xFFFFFFFFu;
+  eqv = 0u;
+  eq_need = 0u;
+  uint32_t prefix = 0u, need = kp;
+#pragma unroll
+  for (int rd = 0; rd < 3; ++rd) {
+    const int sh = 20 - 10 * rd;
+    const uint32_t msk = rd == 0 ? 0x7FFu : 0x3FFu;
+    uint32_t* H = hist + (rd == 0 ? 0 : 1024 + 1024 * rd);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const bool in = (key[r] != 0u) & ((rd == 0) | ((key[r] >> (sh + 10)) == prefix));
+      if (__ballot(in) != 0ull) atomicAdd(&H[(key[r] >> sh) & msk], in ? 1u : 0u);
+    }
+    __syncthreads();
+    const RadixPick p = rd == 0 ? radix_pick<32>(H, need, lane) : radix_pick<16>(H, need, lane);
+    if (rd == 0 && p.total < need) {
+      gt = 0u;
+      return;
+    }
+    need -= p.above;
+    prefix = (prefix << 10) | p.digit;
+    if (need == p.cnt) {
+      const uint32_t lo = prefix << sh;
+      gt = lo == 0u ? 0u : lo - 1u;
+      return;
+    }
+    if (rd == 2) {
+      gt = prefix;
+      eqv = prefix;
+      eq_need = need;
+    }
+  }
+}
 
 // Slice sl (blocks sl kSliceBlocks ..) of sequence x KV head bh: the
 // candidates' keys and ids, ascending by id, to ck / ci (k slots) and their
