@@ -715,9 +715,10 @@ __global__ __launch_bounds__(256, 2) void prefill_rescore_kernel(
 }
 
 // ------------------------------------------------------ fused group pass
-// One wavefront per (kP = prefill_wave_positions(G) consecutive positions,
-// sequence x KV head, split), four of consecutive positions per workgroup.
-// The kP G query rows are the columns of the wavefront's matrix-core tiles
+// One wavefront per (kP consecutive positions, sequence x KV head, split); the
+// four of a workgroup take consecutive positions, or splits of the same ones
+// (prefill_positions, prefill_splits, prefill_wg_groups). The kP G query rows
+// are the columns of the wavefront's matrix-core tiles
 // (16 at most), and it walks once over the union of the blocks its positions
 // select, one 32-token step at a time, with keys and values straight in
 // registers (the bf16 caches hold a step in operand order):
@@ -740,6 +741,9 @@ __global__ __launch_bounds__(256, 2) void prefill_rescore_kernel(
 // another position of the tile attends to: a wavefront whose sums end up not
 // finite repeats its pass with each position multiplying only the tokens that
 // count for it.
+// ONE: one position per wavefront, which walks its selection as it is listed,
+// without forming a union (4 x 8 units at 128K, 1 position 27 -> 20 us; 8 units at
+// 200K in four segments 34 -> 21).
 // One workgroup per query read each query's blocks anew: 138.5 us + 25.9 us
 // for the linear branch for 32 positions at 128K tokens (8 KV heads, 4 heads
 // each, D = 128, 64 blocks of 64), now 132.0 us with the linear branch in it
@@ -751,13 +755,18 @@ constexpr int kSegBlocks = 1024;  // block ids of one pass over the union
 template <int D>
 struct GroupSmem {  // of one wavefront
   uint4 q[3][D / 32][64];         // operands of its columns: q, phi(q) hi, phi(q) lo
-  uint32_t mask[kSegBlocks / 2];  // positions that selected each block (16 bits each)
-  uint16_t list[kSegBlocks];      // blocks of the union, ascending
+  union {
+    struct {
+      uint32_t mask[kSegBlocks / 2];  // positions that selected each block (16 bits each)
+      uint16_t list[kSegBlocks];      // blocks of the union, ascending
+    };
+    int32_t one[SPLA_MAX_TOP_K + 1];  // one position: the blocks it walks
+  };
 };
 
 struct GroupArgs {
   Dims m;
-  int T, n_blk, n_grp, n_split, n_items, stride;
+  int T, P, n_blk, gw, n_grp, n_split, n_items, stride;
   float s, eps;
   uint32_t flags;
   const bf16_t *kc, *vc, *q;
@@ -791,7 +800,7 @@ struct GroupWave {
 
 // One walk over the union of the selections. LIN: with the linear branch.
 // SLOW: each position multiplies only the tokens that count for it.
-template <int D, int BLK, bool LIN, bool SLOW>
+template <int D, int BLK, bool ONE, bool LIN, bool SLOW>
 __device__ __forceinline__ void group_walk(const GroupArgs& a, int bh, GroupWave<D>& s,
                                            GroupSmem<D>& sm) {
   uint32_t* mask = sm.mask;
@@ -799,44 +808,63 @@ __device__ __forceinline__ void group_walk(const GroupArgs& a, int bh, GroupWave
   constexpr int KS = D / 32, MT = D / 16, CPB = BLK / 32;
   const Dims& m = a.m;
   const int lane = threadIdx.x & 63, lg = lane >> 4;
-  for (int seg = 0; seg < s.nbg; seg += kSegBlocks) {
-    // ---- the union of the positions' selections within this segment
-    const int ns = min(kSegBlocks, s.nbg - seg);
-    for (int x = lane; 2 * x < ns; x += 64) mask[x] = 0u;
-    wave_lds_fence();
-    {
-      const int32_t* sp = a.sel + ((int64_t)bh * a.T + s.if0) * m.k;
-      for (int x = lane; x < (s.il0 - s.if0 + 1) * m.k; x += 64) {
-        const int id = sp[x] - seg, pos = s.if0 - s.i0 + x / m.k;
-        if (id >= 0 && id < ns) atomicOr(&mask[id >> 1], 1u << (pos + 16 * (id & 1)));
-      }
-    }
-    wave_lds_fence();
+  const int32_t* sp = a.sel + ((int64_t)bh * a.T + s.if0) * m.k;
+  for (int seg = 0; seg < (ONE ? 1 : s.nbg); seg += kSegBlocks) {
     int n_list = 0;
-    for (int x0 = 0; x0 < ns; x0 += 128) {  // two blocks per lane
-      const int x = x0 + 2 * lane;
-      const uint32_t v = x < ns ? mask[x >> 1] : 0u;
-      // with the linear branch the positions' own block is always walked
-      const bool p0 = (v & 0xFFFFu) || (LIN && seg + x == s.bw);
-      const bool p1 = (v >> 16) || (LIN && seg + x + 1 == s.bw);
-      const uint32_t n = (p0 ? 1u : 0u) + (p1 ? 1u : 0u);
-      const uint32_t incl = wave_incl_scan_u32(n);
-      int pos = n_list + (int)(incl - n);
-      if (p0) list[pos++] = (uint16_t)x;
-      if (p1) list[pos] = (uint16_t)(x + 1);
-      n_list += (int)lane_u32(incl, 63);
+    if constexpr (ONE) {
+      // ---- one position: its selection, 2 block + 1, and 2 block for its own
+      // block where that is walked without being selected
+      bool own = false;
+      for (int x0 = 0; x0 < m.k; x0 += 64) {
+        const int id = x0 + lane < m.k ? sp[x0 + lane] : -1;
+        if (id >= 0) sm.one[x0 + lane] = 2 * id + 1;
+        n_list += __popcll(__ballot(id >= 0));  // (the entries that are there come first)
+        own |= __ballot(id == s.bw) != 0ull;
+      }
+      if (LIN && !own) {
+        if (lane == 0) sm.one[n_list] = 2 * s.bw;
+        ++n_list;
+      }
+      wave_lds_fence();
+    } else {
+      // ---- the union of the positions' selections within this segment
+      const int ns = min(kSegBlocks, s.nbg - seg);
+      for (int x = lane; 2 * x < ns; x += 64) mask[x] = 0u;
+      wave_lds_fence();
+      {
+        for (int x = lane; x < (s.il0 - s.if0 + 1) * m.k; x += 64) {
+          const int id = sp[x] - seg, pos = s.if0 - s.i0 + x / m.k;
+          if (id >= 0 && id < ns) atomicOr(&mask[id >> 1], 1u << (pos + 16 * (id & 1)));
+        }
+      }
+      wave_lds_fence();
+      for (int x0 = 0; x0 < ns; x0 += 128) {  // two blocks per lane
+        const int x = x0 + 2 * lane;
+        const uint32_t v = x < ns ? mask[x >> 1] : 0u;
+        // with the linear branch the positions' own block is always walked
+        const bool p0 = (v & 0xFFFFu) || (LIN && seg + x == s.bw);
+        const bool p1 = (v >> 16) || (LIN && seg + x + 1 == s.bw);
+        const uint32_t n = (p0 ? 1u : 0u) + (p1 ? 1u : 0u);
+        const uint32_t incl = wave_incl_scan_u32(n);
+        int pos = n_list + (int)(incl - n);
+        if (p0) list[pos++] = (uint16_t)x;
+        if (p1) list[pos] = (uint16_t)(x + 1);
+        n_list += (int)lane_u32(incl, 63);
+      }
+      wave_lds_fence();
     }
-    wave_lds_fence();
     const int n_mine = n_list > s.split ? (n_list - s.split + a.n_split - 1) / a.n_split : 0;
     const int n_steps = n_mine * CPB;
     if (n_steps == 0) continue;
     auto entry = [&](int st) {
-      return __builtin_amdgcn_readfirstlane((int)list[s.split + (st / CPB) * a.n_split]);
+      const int at = s.split + (st / CPB) * a.n_split;
+      return __builtin_amdgcn_readfirstlane(ONE ? sm.one[at] : (int)list[at]);
     };
-    auto slot0 = [&](int st, int x) {  // first element of step st, of segment block x
-      int64_t slot = (int64_t)bh * m.nb_cap + seg + x;
+    auto block = [&](int x) { return ONE ? x >> 1 : seg + x; };
+    auto slot0 = [&](int st, int x) {  // first element of step st, of entry x
+      int64_t slot = (int64_t)bh * m.nb_cap + block(x);
       if (a.table) {
-        const int pg = block_page(m, a.table, bh, seg + x);
+        const int pg = block_page(m, a.table, bh, block(x));
         slot = (int64_t)(pg < 0 ? 0 : pg) * m.hkv + bh % m.hkv;
       }
       return (slot * BLK + (st % CPB) * 32) * D;
@@ -859,9 +887,11 @@ __device__ __forceinline__ void group_walk(const GroupArgs& a, int bh, GroupWave
     load_k(e0);
     load_v(e0);
     for (int st = 0; st < n_steps; ++st) {
-      const int id = seg + x, base = id * BLK + (st % CPB) * 32;
-      const uint32_t bits = (uint32_t)__builtin_amdgcn_readfirstlane(
-                                (int)(mask[x >> 1] >> (16 * (x & 1)))) & ((1u << s.P) - 1u);
+      const int id = block(x), base = id * BLK + (st % CPB) * 32;
+      const uint32_t bits =
+          ONE ? (uint32_t)(x & 1)
+              : (uint32_t)__builtin_amdgcn_readfirstlane((int)(mask[x >> 1] >> (16 * (x & 1)))) &
+                    ((1u << s.P) - 1u);
       // the next step: its keys are loaded when this step's are used up
       const int nx = st + 1 < n_steps ? st + 1 : st;
       x = entry(nx);
@@ -1017,8 +1047,10 @@ __device__ __forceinline__ void group_walk(const GroupArgs& a, int bh, GroupWave
   }
 }
 
-// The sums before any block: zero, or minus the global term (LIN, split 0):
-// al = -S_x^T phi(q), zl = -<phi(q), z_x>, x the xw-th block of the chunk.
+// The sums before any block: zero, or minus the global term (LIN): al = -S_x^T
+// phi(q), zl = -<phi(q), z_x>, x the xw-th block of the chunk. Its coordinate
+// tiles are dealt out over the splits (in one of them they took as long as four
+// to six steps), zl is split 0's.
 template <int D, bool LIN>
 __device__ __forceinline__ void group_start(const GroupArgs& a, int bh, int xw, GroupWave<D>& s,
                                             const GroupSmem<D>& sm) {
@@ -1028,28 +1060,37 @@ __device__ __forceinline__ void group_start(const GroupArgs& a, int bh, int xw, 
   s.l_run = s.zl = 0.f;
 #pragma unroll
   for (int t = 0; t < MT; ++t) s.ax[t] = s.al[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  if (!LIN || s.split != 0) return;
+  if constexpr (!LIN) return;
   const float* zp = a.z_pre + ((int64_t)bh * a.n_blk + xw) * D + 8 * lg;
   const uint4* sh = a.s_hi + ((int64_t)bh * a.n_blk + xw) * (D * D / 8) + lane;
   const uint4* sl = a.s_lo + ((int64_t)bh * a.n_blk + xw) * (D * D / 8) + lane;
+  if (s.split == 0) {
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    const bf16x8 qh = __builtin_bit_cast(bf16x8, sm.q[1][ks][lane]);
-    const bf16x8 ql = __builtin_bit_cast(bf16x8, sm.q[2][ks][lane]);
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 qh = __builtin_bit_cast(bf16x8, sm.q[1][ks][lane]);
+      const bf16x8 ql = __builtin_bit_cast(bf16x8, sm.q[2][ks][lane]);
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      s.zl = fmaf(-((float)qh[e] + (float)ql[e]), zp[32 * ks + e], s.zl);
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const bf16x8 ah = __builtin_bit_cast(bf16x8, sh[(t * KS + ks) * 64]);
-      const bf16x8 aw = __builtin_bit_cast(bf16x8, sl[(t * KS + ks) * 64]);
-      s.al[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw, qh, s.al[t], 0, 0, 0);
-      s.al[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, ql, s.al[t], 0, 0, 0);
-      s.al[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, qh, s.al[t], 0, 0, 0);
+      for (int e = 0; e < 8; ++e)
+        s.zl = fmaf(-((float)qh[e] + (float)ql[e]), zp[32 * ks + e], s.zl);
     }
   }
+  const int t0 = s.split < MT ? s.split : -1, ts = min(a.n_split, MT);
 #pragma unroll
-  for (int t = 0; t < MT; ++t) s.al[t] = -s.al[t];
+  for (int t = 0; t < MT; ++t) {
+    if (t % ts != t0) continue;  // uniform
+    floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 qh = __builtin_bit_cast(bf16x8, sm.q[1][ks][lane]);
+      const bf16x8 ql = __builtin_bit_cast(bf16x8, sm.q[2][ks][lane]);
+      const bf16x8 ah = __builtin_bit_cast(bf16x8, sh[(t * KS + ks) * 64]);
+      const bf16x8 aw = __builtin_bit_cast(bf16x8, sl[(t * KS + ks) * 64]);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw, qh, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, ql, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, qh, acc, 0, 0, 0);
+    }
+    s.al[t] = -acc;
+  }
 }
 
 // Whether any live column's sums are infinite or NaN.
@@ -1064,7 +1105,7 @@ __device__ __forceinline__ bool group_not_finite(const GroupWave<D>& s) {
   return __ballot(bad && s.live) != 0ull;
 }
 
-template <int D, int BLK>
+template <int D, int BLK, bool ONE>
 __global__ __launch_bounds__(256, 2) void prefill_group_kernel(GroupArgs a) {
   constexpr int KS = D / 32, MT = D / 16;
   __shared__ GroupSmem<D> lds[4];
@@ -1072,20 +1113,21 @@ __global__ __launch_bounds__(256, 2) void prefill_group_kernel(GroupArgs a) {
   const int per = (int)(gridDim.x / 8);
   const int item = ((int)blockIdx.x % 8) * per + (int)blockIdx.x / 8;  // one XCD: one run of items
   if (item >= a.n_items) return;
-  const int split = item % a.n_split, gq = item / a.n_split;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int gw = a.gw, wg_splits = a.n_split * gw / 4;  // workgroups that share gw groups
+  const int split = item % wg_splits * (4 / gw) + w / gw, gq = item / wg_splits;
   const int bh = gq / a.n_grp, gi = a.n_grp - 1 - gq % a.n_grp;  // longest prefixes first
   const int b = bh / m.hkv, h = bh % m.hkv, G = m.group, T = a.T;
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int c = lane & 15, lg = lane >> 4;
   GroupSmem<D>& sm = lds[w];
   GroupWave<D> s;
-  const int P = prefill_wave_positions(G);
+  const int P = ONE ? 1 : a.P;
   s.P = P;
   s.split = split;
   chunk_bounds(m, a.seq_lens, b, T, &s.L0, &s.nv);
   const int L0 = s.L0, nv = s.nv;
   // chunk positions of the wavefront (aligned in the sequence): i0 .. i0 + P - 1
-  const int i0 = (L0 / (4 * P) + gi) * 4 * P + P * w - L0;
+  const int i0 = (L0 / (gw * P) + gi) * gw * P + P * (w % gw) - L0;
   if (i0 >= T || i0 + P <= 0) return;
   const int if0 = max(i0, 0), il0 = min(i0 + P, T) - 1;
   s.i0 = i0;
@@ -1147,18 +1189,18 @@ __global__ __launch_bounds__(256, 2) void prefill_group_kernel(GroupArgs a) {
   wave_lds_fence();
   if (lin) {
     group_start<D, true>(a, bh, xw, s, sm);
-    group_walk<D, BLK, true, false>(a, bh, s, sm);
+    group_walk<D, BLK, ONE, true, false>(a, bh, s, sm);
   } else {
     group_start<D, false>(a, bh, xw, s, sm);
-    group_walk<D, BLK, false, false>(a, bh, s, sm);
+    group_walk<D, BLK, ONE, false, false>(a, bh, s, sm);
   }
   if (group_not_finite<D>(s)) {
     if (lin) {
       group_start<D, true>(a, bh, xw, s, sm);
-      group_walk<D, BLK, true, true>(a, bh, s, sm);
+      group_walk<D, BLK, ONE, true, true>(a, bh, s, sm);
     } else {
       group_start<D, false>(a, bh, xw, s, sm);
-      group_walk<D, BLK, false, true>(a, bh, s, sm);
+      group_walk<D, BLK, ONE, false, true>(a, bh, s, sm);
     }
   }
   auto& ax = s.ax;
@@ -1247,8 +1289,8 @@ static void prefill_select_r(const PrefSelectArgs& a, hipStream_t st) {
 
 template <int D, int BLK>
 static void prefill_group_db(const GroupArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((prefill_group_kernel<D, BLK>), dim3((unsigned)align_up(a.n_items, 8)),
-                     dim3(256), 0, st, a);
+  auto kern = a.P == 1 ? prefill_group_kernel<D, BLK, true> : prefill_group_kernel<D, BLK, false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)align_up(a.n_items, 8)), dim3(256), 0, st, a);
 }
 
 template <int D>
@@ -1352,9 +1394,11 @@ static hipError_t prefill_chunk_d(const Dims& m, const spla_config& cfg, const s
   a.m = m;
   a.T = T;
   a.n_blk = n_blk;
-  a.n_grp = prefill_groups(m, T);
+  a.P = prefill_positions(m, T);
   a.n_split = prefill_splits(m, T);
-  a.n_items = m.bh * a.n_grp * a.n_split;
+  a.gw = prefill_wg_groups(a.n_split);
+  a.n_grp = prefill_groups(T, a.gw * a.P);
+  a.n_items = m.bh * a.n_grp * (a.n_split * a.gw / 4);
   a.stride = ws.part_stride;
   a.s = cfg.softmax_scale > 0.f ? cfg.softmax_scale : (float)(1.0 / sqrt((double)m.d));
   a.eps = cfg.rms_eps;

@@ -237,33 +237,50 @@ SPLA_HD bool step_fusable(const Dims& m) { return use_mfma_sparse(m) && step_pre
 // 128: 64 x 8 units of B = 32 run chunks of 97).
 constexpr int kPrefillMinChunk = 32, kPrefillMaxChunk = 1024;
 constexpr int64_t kPrefillBytes = 320 << 20;
-constexpr int kPrefillFill = 512;   // group-pass workgroups to aim for (two per compute unit)
-constexpr int kPrefillMaxSplit = 16;  // workgroups that share one group's blocks at most
+constexpr int kPrefillFill = 2048;  // group-pass wavefronts to aim for (two per SIMD)
+constexpr int kPrefillMaxSplit = 32;  // wavefronts that share one group's blocks at most
 
 // The chunked prefill covers the matrix-core shapes (bf16, G <= 8); the other
 // shapes run position by position (the single-token append, then a decode).
 SPLA_HD bool use_chunked_prefill(const Dims& m) { return use_mfma_sparse(m); }
 
-// Query positions per wavefront of its group pass: a power of two with at
-// most 16 query rows (the columns of a matrix-core tile). A workgroup takes
-// four times as many consecutive positions, aligned in the sequence, so that
-// a wavefront's positions lie in one block.
+// Query positions per wavefront of its group pass, at most: a power of two with
+// at most 16 query rows (the columns of a matrix-core tile). They are aligned
+// in the sequence, so that a wavefront's positions lie in one block.
 SPLA_HD int prefill_wave_positions(int G) { return G <= 1 ? 16 : G <= 2 ? 8 : G <= 4 ? 4 : 2; }
-// Blocks, and groups of positions, that T consecutive tokens touch at most.
+// Blocks, and groups of P positions, that T consecutive tokens touch at most.
 SPLA_HD int prefill_blocks(const Dims& m, int T) { return (T + m.B - 2) / m.B + 1; }
-SPLA_HD int prefill_groups(const Dims& m, int T) {
-  const int qw = 4 * prefill_wave_positions(m.group);
-  return (T + qw - 2) / qw + 1;
+SPLA_HD int prefill_groups(int T, int P) { return (T + P - 2) / P + 1; }
+// Positions per wavefront for a chunk of T. Where one each gives no wavefront (of
+// kPrefillFill) more than eight 32-token steps, the call waits for the longest
+// chain rather than for the chip, and one is shortest: one head, 32 positions of
+// k = 16 blocks of 64, 21 us against 35 for sixteen each; 8 units of 4 heads, 16
+// positions 26 against 33 for four each. Past that as many as fit are about as fast
+// for queries that share few blocks, and up to 2.5 times as fast for those that
+// share them (4 x 8 units, k = 64, 16 positions on the same blocks 84 us against
+// 156).
+SPLA_HD int prefill_positions(const Dims& m, int T) {
+  const int64_t steps = (int64_t)m.bh * T * m.k * (m.B / 32);
+  return steps <= 8 * kPrefillFill ? 1 : prefill_wave_positions(m.group);
 }
-// Workgroups sharing the blocks of one group: enough to fill the GPU, each
-// with at least four 32-token steps of one query's selection.
+// Wavefronts that share the blocks of one group: enough to fill the GPU, each
+// with at least two steps of one query's selection (past 16, with four: at two a
+// further wavefront's start and record cost what it saves); 1, 2 or a multiple of 4.
 SPLA_HD int prefill_splits(const Dims& m, int T) {
-  const int64_t groups = (int64_t)m.bh * prefill_groups(m, T);
+  const int64_t groups = m.bh * ceil_div(T, prefill_positions(m, T));
+  const int64_t steps = (int64_t)m.k * (m.B / 32);
+  int64_t most = ceil_div(steps, 2);
+  if (most > 16) most = steps / 4 > 16 ? steps / 4 : 16;
+  if (most > kPrefillMaxSplit) most = kPrefillMaxSplit;
   int64_t n = ceil_div(kPrefillFill, groups);
-  const int64_t most = ceil_div((int64_t)m.k * (m.B / 32), 4);
   n = n < most ? n : most;
-  return (int)(n < kPrefillMaxSplit ? n : kPrefillMaxSplit);
+  if (n > 2) n = (n + 2) / 4 * 4 <= most ? (n + 2) / 4 * 4 : n < 4 ? 2 : n / 4 * 4;
+  return (int)n;
 }
+// Consecutive groups of positions per workgroup of four wavefronts, which share
+// what is left: a workgroup's wavefronts have work, or none of them (idle ones
+// would hold the others' places: 16 x 8 units, 32 positions 164 us against 223).
+SPLA_HD int prefill_wg_groups(int n_split) { return n_split >= 4 ? 1 : 4 / n_split; }
 
 // part_s and part_z, then e_vals to q_norm2, then part lie over one another: each
 // group is written after the one before it was last read (one stream).
@@ -317,11 +334,11 @@ SPLA_HD PrefillWs prefill_chunk_layout(const Dims& m, int T) {
   off = base;
   // records: the most that a chunk of t <= T positions splits into, t
   // n_split(t) per (sequence, KV head): n_split is largest for one position,
-  // below kPrefillFill / groups + 1, and 1 from F = kPrefillFill (positions per
+  // below kPrefillFill / groups + 3, and 1 from F = kPrefillFill (positions per
   // group) / bh positions on (groups >= bh t / positions per group)
-  const int64_t F = ceil_div(kPrefillFill * 4 * prefill_wave_positions(m.group), m.bh);
+  const int64_t F = ceil_div(kPrefillFill * prefill_wave_positions(m.group), m.bh);
   const int64_t n1 = prefill_splits(m, 1), t = T < F ? T : F;
-  const int64_t rows = n1 > 1 ? (t * n1 < t + F ? t * n1 : t + F) : 0;
+  const int64_t rows = n1 > 1 ? (t * n1 < 3 * t + F ? t * n1 : 3 * t + F) : 0;
   w.part = take(m.bh * rows * w.part_stride * 4);
   w.total = w.total > off ? w.total : off;
   return w;

@@ -30,11 +30,16 @@ def test_records_fit(shape):
     """Rows of records a chunk of t positions writes (t per split of its groups), by
     the rule that sets the number of splits, against what the buffer for T holds."""
     b, hkv, g, d, B, k, cap = shape
-    bh, qw = b * hkv, 4 * (16 if g <= 1 else 8 if g <= 2 else 4 if g <= 4 else 2)
+    bh, steps = b * hkv, k * (B // 32)
+    fit = 16 if g <= 1 else 8 if g <= 2 else 4 if g <= 4 else 2  # positions per wavefront
 
     def splits(t):
-        groups = bh * ((t + qw - 2) // qw + 1)
-        return min(-(-512 // groups), -(-k * (B // 32) // 4), 16)
+        groups = bh * -(-t // (1 if bh * t * steps <= 16384 else fit))
+        most = min(-(-steps // 2), max(16, steps // 4), 32)
+        n = min(-(-2048 // groups), most)
+        if n > 2:  # the nearest multiple of four within most
+            n = (n + 2) // 4 * 4 if (n + 2) // 4 * 4 <= most else 2 if n < 4 else n // 4 * 4
+        return n
 
     row = (48 + 2 * g * d) * 4
     for T in (1, 2, 7, 31, 32, 33, 64, 100, 256, 1000):
