@@ -15,7 +15,8 @@
 //                           each statistics tile is loaded once
 //   prefill_select_kernel   every query's top-k; prefill_rescore_kernel and a
 //                           second selection for the queries whose cutoff the
-//                           rounding of the scores could move
+//                           rounding of the scores could move (short chunks are
+//                           scored by prefill_rescore_kernel alone)
 //   prefill_group_kernel    the fused exact + linear pass for groups of
 //                           consecutive queries over the union of their
 //                           selections
@@ -508,6 +509,7 @@ struct PrefSelectArgs {
   const float* q_norm2;    // |q|^2 per query row
   float s;
   int listed;  // select the listed queries (else every query, listing some)
+  int exact;   // the masses have the decode's sums already: list none
 };
 
 template <int R, bool WIN, int NT, int SWN, int GMAX>
@@ -553,7 +555,7 @@ __global__ __launch_bounds__(NT) void prefill_select_kernel(PrefSelectArgs a) {
     const int bh = vh / a.T, i = vh % a.T, L = length(vh);
     if (!a.listed && per > 1 && (L + m.B - 1) / m.B <= m.k) continue;  // uniform; written above
     float span = 0.f;
-    if (!a.listed && (L + m.B - 1) / m.B > m.k) {  // uniform
+    if (!a.listed && !a.exact && (L + m.B - 1) / m.B > m.k) {  // uniform
       if (bh != bh_max) {
         int L0, nv;
         chunk_bounds(m, a.seq_lens, bh / m.hkv, a.T, &L0, &nv);
@@ -595,41 +597,68 @@ __global__ __launch_bounds__(NT) void prefill_select_kernel(PrefSelectArgs a) {
 // Where blocks repeat, every query can be listed (ties at the cutoff): 8192
 // queries over 32 tiles of 64 blocks took 7400 us with one query's G columns at
 // a time, 820 with kP.
-template <int D>
-__global__ __launch_bounds__(256, 2) void prefill_rescore_kernel(
+// kAll: every query, in place of prefill_score_kernel (exact_scores); kAllOneTile:
+// they fill one column tile at most, so the statistics are read quarter by quarter
+// instead of kept (156 registers instead of 256, three workgroups per compute unit
+// instead of two: 4 x 8 units of 2048 blocks 28 -> 23 us).
+enum { kListed, kAll, kAllOneTile };
+
+// Whether a chunk's queries are scored with the decode's sums at once, which takes
+// 16 columns at a time but no listing, rescoring and second selection (two
+// launches, and where many are listed more than the first): up to two tiles of
+// columns, up to one workgroup's worth of work per place on the chip, and with
+// strided windows, where blocks that share their best window tie and most queries
+// are listed, up to eight. Score and selections, us, listing against at once:
+// 4 x 8 units of 2048 blocks, 1 / 2 / 4 / 8 column tiles 57 / 65 / 68 / 87 against
+// 33 / 52 / 77 / 123; 8 units of 128 blocks, 4 / 8 / 16 tiles 26 / 24 / 26 against
+// 20 / 25 / 37; 4 x 8 units of 2048 windows, 1 / 4 / 8 / 16 tiles 80 / 125 / 195 /
+// 328 against 42 / 109 / 187 / 343.
+static bool exact_scores(const Dims& m, int T) {
+  const int64_t n_ct = ceil_div(T, 16 / m.group);
+  return n_ct <= (windowed(m) ? 8 : 2) ||
+         n_ct * m.n_tiles * m.bh <= 2 * (int64_t)compute_units();
+}
+
+template <int D, int WHICH>
+__global__ __launch_bounds__(256, WHICH == kAllOneTile ? 3 : 2) void prefill_rescore_kernel(
     Dims m, int T_, int W, const float* __restrict__ stats, const int32_t* __restrict__ seq_lens,
     const bf16_t* __restrict__ q, double s, int first_order, const double* __restrict__ ell_part,
     int32_t* __restrict__ near, float* __restrict__ e_vals, double* __restrict__ tile_part) {
   constexpr int NK = D / 4, NQ = D / 32;  // k-steps, partials per quarter of the coordinates
+  constexpr bool ALL = WHICH != kListed, ONE = WHICH == kAllOneTile;
   __shared__ float s_c[2][NK][64];        // s q and s^2 q^2 / 2, as operands
   __shared__ double s_mx[4][16], s_sum[4][16];
   const int G = m.group, kP = 16 / G, nbp = m.n_tiles * kTileBlocks;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int li = lane & 15, lg = lane >> 4;
   const NearLists nl = near_lists(m, near);
-  const int tile = blockIdx.x, bh = blockIdx.z, n_near = nl.count[bh];
+  const int tile = blockIdx.x, bh = blockIdx.z, n_near = ALL ? T_ : nl.count[bh];
   if ((int)blockIdx.y * kP >= n_near) return;
   int L0, nv;
   chunk_bounds(m, seq_lens, bh / m.hkv, T_, &L0, &nv);
   if (tile * kTileBlocks * m.us >= L0 + nv) return;  // past every query's tokens
-  const int32_t* list = nl.list + (int64_t)bh * T_;
+  if (ALL && (L0 + nv + m.B - 1) / m.B <= m.k) return;  // every query selects every block
+  auto position = [&](int x) { return ALL ? x : nl.list[(int64_t)bh * T_ + x]; };
   float pm[NK], pv[NK];
-  {
-    const float* st = stats + stats_off4(m, bh, (int64_t)tile * kTileBlocks, 0, 0);  // uniform
-    const float* st2 = first_order ? st : st + D / 4 * kTileBlocks * 4;
+  const float* st = stats + stats_off4(m, bh, (int64_t)tile * kTileBlocks, 0, 0);  // uniform
+  const float* st2 = first_order ? st : st + D / 4 * kTileBlocks * 4;
+  auto load = [&](int qt) {  // a quarter of the coordinates
     const uint32_t o = (uint32_t)(16 * w + li) * 4u + (uint32_t)lg;
 #pragma unroll
-    for (int j = 0; j < NK; ++j) {
+    for (int j = 2 * NQ * qt; j < 2 * NQ * (qt + 1); ++j) {
       pm[j] = (st + j * kTileBlocks * 4)[o];
       pv[j] = (st2 + j * kTileBlocks * 4)[o];
     }
-  }
+  };
+  auto quarter = [](int qp) { return qp / 2 + 2 * (qp % 2); };
+#pragma unroll
+  for (int qp = 0; qp < (ONE ? 1 : 4); ++qp) load(quarter(qp));
   const int u_lane = tile * kTileBlocks + 16 * w + 4 * lg;  // this lane's first result row
   for (int x0 = (int)blockIdx.y * kP; x0 < n_near; x0 += (int)gridDim.y * kP) {
     const int nc = min(kP, n_near - x0) * G;  // columns in use
     {
       const int c = min(li, nc - 1), g = c % G;
-      const bf16_t* qr = q + (((int64_t)list[x0 + c / G] * m.batch + bh / m.hkv) * m.hq +
+      const bf16_t* qr = q + (((int64_t)position(x0 + c / G) * m.batch + bh / m.hkv) * m.hq +
                               bh % m.hkv * G + g) * D + lg;
 #pragma unroll
       for (int jj = 0; jj < NK / 4; ++jj) {
@@ -643,7 +672,8 @@ __global__ __launch_bounds__(256, 2) void prefill_rescore_kernel(
     double am[2][4], av[2][4];  // quarters qt and qt + 2 of the coordinates added, result row
 #pragma unroll
     for (int qp = 0; qp < 4; ++qp) {
-      const int qt = qp / 2 + 2 * (qp % 2);
+      const int qt = quarter(qp);
+      if (ONE && qp < 3) load(quarter(qp + 1));
       double dm[4] = {0.0, 0.0, 0.0, 0.0}, dv[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int jp = 0; jp < NQ; ++jp) {
@@ -668,7 +698,7 @@ __global__ __launch_bounds__(256, 2) void prefill_rescore_kernel(
       __builtin_amdgcn_sched_barrier(0);  // (operands of one quarter at a time in registers)
     }
     // this lane's column: position i, head g of the group
-    const int c = min(li, nc - 1), i = list[x0 + c / G], g = c % G;
+    const int c = min(li, nc - 1), i = position(x0 + c / G), g = c % G;
     const int64_t vh = (int64_t)bh * T_ + i;
     const int L = L0 + min(i + 1, nv), nu = (L + m.us - 1) / m.us;
     double ell[4];
@@ -711,6 +741,7 @@ __global__ __launch_bounds__(256, 2) void prefill_rescore_kernel(
       double2* tp = reinterpret_cast<double2*>(tile_part) + (vh * G + g) * m.n_tiles + tile;
       *tp = make_double2(tmx, sum);
     }
+    if (ONE) break;
   }
 }
 
@@ -1328,17 +1359,32 @@ static hipError_t prefill_chunk_d(const Dims& m, const spla_config& cfg, const s
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark_phase(ev, SPLA_PHASE_LINEAR, true, st);
   // 3. block scores of every query; the queries are split over more
-  // workgroups where the tiles alone leave compute units idle
+  // workgroups where the tiles alone leave compute units idle. exact: with the
+  // decode's sums at once, so that no query is listed
   mark_phase(ev, SPLA_PHASE_SCORE, false, st);
   const int64_t tiles = (int64_t)m.n_tiles * m.bh, n_cg = ceil_div((int64_t)T * m.group, 64);
-  const int64_t qs = ceil_div(4 * (int64_t)compute_units(), tiles);
-  hipLaunchKernelGGL((prefill_score_kernel<D>),
-                     dim3((unsigned)m.n_tiles, (unsigned)(qs < n_cg ? qs : n_cg), (unsigned)m.bh),
-                     dim3(256), 0, st, m, T, W, (const float*)c.blk_stats,
-                     (const int32_t*)c.seq_lens, q, s_score, fo,
-                     (const double*)(base + ws.ell_part), (float*)(base + ws.e_vals),
-                     (double*)(base + ws.tile_part), (float2*)(base + ws.unit_max),
-                     (float*)(base + ws.q_norm2));
+  const int64_t n_ct = ceil_div(T, 16 / m.group);
+  const bool exact = exact_scores(m, T);
+  // (two workgroups per compute unit at a time, and as many again)
+  const int64_t qs = ceil_div((exact ? 2 : 4) * (int64_t)compute_units(), tiles);
+  auto rescore = [&](auto kern, int64_t most) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)m.n_tiles, (unsigned)(qs < most ? qs : most), (unsigned)m.bh),
+                       dim3(256), 0, st, m, T, W, (const float*)c.blk_stats,
+                       (const int32_t*)c.seq_lens, q, s_score, fo,
+                       (const double*)(base + ws.ell_part), (int32_t*)(base + ws.near),
+                       (float*)(base + ws.e_vals), (double*)(base + ws.tile_part));
+  };
+  if (exact)
+    rescore(n_ct == 1 ? prefill_rescore_kernel<D, kAllOneTile> : prefill_rescore_kernel<D, kAll>,
+            n_ct);
+  else
+    hipLaunchKernelGGL((prefill_score_kernel<D>),
+                       dim3((unsigned)m.n_tiles, (unsigned)(qs < n_cg ? qs : n_cg), (unsigned)m.bh),
+                       dim3(256), 0, st, m, T, W, (const float*)c.blk_stats,
+                       (const int32_t*)c.seq_lens, q, s_score, fo,
+                       (const double*)(base + ws.ell_part), (float*)(base + ws.e_vals),
+                       (double*)(base + ws.tile_part), (float2*)(base + ws.unit_max),
+                       (float*)(base + ws.q_norm2));
   if ((e = hipGetLastError()) != hipSuccess) return e;
   mark_phase(ev, SPLA_PHASE_SCORE, true, st);
   // 4. selection of every query: without windows and up to 2048 blocks, 256
@@ -1360,14 +1406,12 @@ static hipError_t prefill_chunk_d(const Dims& m, const spla_config& cfg, const s
   sa.q_norm2 = (const float*)(base + ws.q_norm2);
   sa.s = (float)s_score;
   sa.listed = 0;
+  sa.exact = exact;
   auto select = [&](auto f) {
     f(sa, st);
+    if (exact) return;
     sa.listed = 1;
-    hipLaunchKernelGGL((prefill_rescore_kernel<D>),
-                       dim3((unsigned)m.n_tiles, (unsigned)(qs < n_cg ? qs : n_cg), (unsigned)m.bh),
-                       dim3(256), 0, st, m, T, W, (const float*)c.blk_stats, (const int32_t*)c.seq_lens, q,
-                       s_score, fo, (const double*)(base + ws.ell_part), sa.near,
-                       (float*)(base + ws.e_vals), (double*)(base + ws.tile_part));
+    rescore(prefill_rescore_kernel<D, kListed>, n_cg);
     f(sa, st);
   };
   if (windowed(m)) {
