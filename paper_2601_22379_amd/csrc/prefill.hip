@@ -777,10 +777,10 @@ __global__ __launch_bounds__(256, WHICH == kAllOneTile ? 3 : 2) void prefill_res
 // 200K in four segments 34 -> 21).
 // One workgroup per query read each query's blocks anew: 138.5 us + 25.9 us
 // for the linear branch for 32 positions at 128K tokens (8 KV heads, 4 heads
-// each, D = 128, 64 blocks of 64), now 132.0 us with the linear branch in it
+// each, D = 128, 64 blocks of 64), now 115.4 us with the linear branch in it
 // (random queries: hardly a block is shared). A whole prefill of a prompt,
-// where neighbours share most of their blocks, went from 4438 to 180 us, and
-// one that continues 126K tokens from 2487 to 1094 us.
+// where neighbours share most of their blocks, went from 4440 to 180 us, and
+// one that continues 126K tokens from 2490 to 1145 us.
 constexpr int kSegBlocks = 1024;  // block ids of one pass over the union
 
 template <int D>

@@ -280,10 +280,10 @@ struct ScoreSmem {
 // then comes when those loads are on their way, so that the length it looks at
 // (a load of its own) does not hold up the stream. That order costs a full
 // cache 2 % (32K tokens 23.2 -> 23.8 us, 128K 29.0 -> 29.6 us), so only a step,
-// whose items need the length early anyway, asks early. gate.load() runs behind the statistics loads and before the
-// barrier, gate.apply(A, bi, qt) after it on this lane's unit bi of the tile,
-// quarter qt of its coordinates; gate.length() is the length to score with.
-// False if the tile was not live.
+// whose items need the length early anyway, asks early. gate.load() runs behind
+// the statistics loads and before the barrier, gate.apply(A, bi, qt) after it on
+// this lane's unit bi of the tile, quarter qt of its coordinates; gate.length()
+// is the length to score with. False if the tile was not live.
 struct NoGate {
   static constexpr bool on = false, early = false;
 };
