@@ -35,8 +35,9 @@ def test_listed_queries_select_as_a_decode(group, d, B, kw):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     dev = torch.device("cuda:0")
-    w = si.custom("ties", 2, 2 * group, 2, d, B, 7, [4500, 3000], kind="iid", code=300 + group,
-                  capacity=4736)
+    # (wide and long enough that the queries are listed rather than scored exactly at once)
+    w = si.custom("ties", 6, 2 * group, 2, d, B, 7, [4500, 3000] * 3, kind="iid",
+                  code=300 + group, capacity=65536)
     T = 37
     kn, vn, q = chunk_inputs(w, T, list(w.lengths))
     gamma = torch.from_numpy(si.gen_gamma(w)).to(dev)

@@ -53,10 +53,12 @@ def test_decode_and_step(name):
     both(name, call)
 
 
+# 3 positions: the last step holds rows of the prefix, which carry linear weights; 41:
+# consecutive positions share a wavefront
+@pytest.mark.parametrize("T", [3, 41])
 @pytest.mark.parametrize("name", list(CASES))
-def test_prefill(name):
+def test_prefill(name, T):
     def call(w, cache, dev):
-        T = 3  # the last step holds rows of the prefix: those carry linear weights
         q = torch.cat([H.to_dev(si.gen_q_batch(w, t), w, dev)[None] for t in range(T)])
         g = torch.Generator().manual_seed(4)
         rows = [torch.randn((T, w.batch, w.n_kv_heads, w.head_dim), generator=g).to(dev, q.dtype)
