@@ -263,24 +263,47 @@ SPLA_HD int prefill_positions(const Dims& m, int T) {
   const int64_t steps = (int64_t)m.bh * T * m.k * (m.B / 32);
   return steps <= 8 * kPrefillFill ? 1 : prefill_wave_positions(m.group);
 }
-// Wavefronts that share the blocks of one group: enough to fill the GPU, each
-// with at least two steps of one query's selection (past 16, with four: at two a
-// further wavefront's start and record cost what it saves); 1, 2 or a multiple of 4.
-SPLA_HD int prefill_splits(const Dims& m, int T) {
-  const int64_t groups = m.bh * ceil_div(T, prefill_positions(m, T));
-  const int64_t steps = (int64_t)m.k * (m.B / 32);
-  int64_t most = ceil_div(steps, 2);
-  if (most > 16) most = steps / 4 > 16 ? steps / 4 : 16;
-  if (most > kPrefillMaxSplit) most = kPrefillMaxSplit;
-  int64_t n = ceil_div(kPrefillFill, groups);
-  n = n < most ? n : most;
-  if (n > 2) n = (n + 2) / 4 * 4 <= most ? (n + 2) / 4 * 4 : n < 4 ? 2 : n / 4 * 4;
-  return (int)n;
-}
 // Consecutive groups of positions per workgroup of four wavefronts, which share
-// what is left: a workgroup's wavefronts have work, or none of them (idle ones
-// would hold the others' places: 16 x 8 units, 32 positions 164 us against 223).
-SPLA_HD int prefill_wg_groups(int n_split) { return n_split >= 4 ? 1 : 4 / n_split; }
+// the splits that are left: a workgroup's wavefronts have work, or none of them
+// (idle ones would hold the others' places: 16 x 8 units, 32 positions 164 us
+// against 223).
+SPLA_HD int prefill_wg_groups(int n_split) {
+  return n_split % 4 == 0 ? 1 : n_split % 2 == 0 ? 2 : 4;
+}
+// Wavefronts that may share the blocks of one group: each takes at least two steps
+// of one query's selection (past 16, four: at two a further wavefront's start and
+// record cost what it saves).
+SPLA_HD int prefill_most_splits(const Dims& m) {
+  const int steps = m.k * (m.B / 32), n = (steps + 1) / 2;
+  const int most = n <= 16 ? n : steps / 4 > 16 ? steps / 4 : 16;
+  return most < kPrefillMaxSplit ? most : kPrefillMaxSplit;
+}
+// ... and how many do: the number n with the shortest time by the steps of ceil(k /
+// n) blocks (a wavefront takes whole ones) and two for the start, times the rounds
+// its places make of kPrefillFill, up to two. A wavefront alone on its SIMD runs
+// little faster than two (half a round 0.8), and the ends of a first round fill with
+// a second (half a round 0.7, three quarters 0.85). 4 x 8 units at 128K, 8 positions:
+// 16 splits (1024 places) 127 us, 32 (2048) 97; 96 positions: 3 (2304) 768, 4 (3072)
+// 621; 8 units of 5 heads, 48 positions: 12 (2304) 82, 10 (1920) 69.
+SPLA_HD int prefill_splits(const Dims& m, int T) {
+  const int64_t ng = ceil_div(T, prefill_positions(m, T));
+  const int most = prefill_most_splits(m), cpb = m.B / 32;
+  int best = 1;
+  int64_t best_cost = 0;
+  for (int n = 1; n <= most; ++n) {
+    if (n > 1 && m.bh * ng * n > 2 * kPrefillFill) break;
+    const int64_t w = m.bh * align_up(ng, prefill_wg_groups(n)) * n;
+    const int64_t full = w / kPrefillFill, r = 4 * (w % kPrefillFill) / kPrefillFill;  // quarters
+    const bool any = w % kPrefillFill != 0, half = 2 * (w % kPrefillFill) <= kPrefillFill;
+    const int64_t last = !any ? 0 : full == 0 ? (half ? 80 : 100) : half ? 70 : r < 3 ? 85 : 100;
+    const int64_t cost = (100 * full + last) * (ceil_div(m.k, n) * cpb + 2);
+    if (n == 1 || cost < best_cost) {
+      best = n;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
 
 // part_s and part_z, then e_vals to q_norm2, then part lie over one another: each
 // group is written after the one before it was last read (one stream).
@@ -332,13 +355,13 @@ SPLA_HD PrefillWs prefill_chunk_layout(const Dims& m, int T) {
   w.q_norm2 = take(nq * m.group * 4);
   w.total = w.total > off ? w.total : off;
   off = base;
-  // records: the most that a chunk of t <= T positions splits into, t
-  // n_split(t) per (sequence, KV head): n_split is largest for one position,
-  // below kPrefillFill / groups + 3, and 1 from F = kPrefillFill (positions per
-  // group) / bh positions on (groups >= bh t / positions per group)
+  // records: the most that a chunk of t <= T positions splits into, t n_split(t)
+  // per (sequence, KV head): n_split <= prefill_most_splits, and groups n_split <= 2
+  // kPrefillFill with groups >= bh t / positions per group, so no splits past F =
+  // kPrefillFill (positions per group) / bh positions and 2 F rows at most
   const int64_t F = ceil_div(kPrefillFill * prefill_wave_positions(m.group), m.bh);
-  const int64_t n1 = prefill_splits(m, 1), t = T < F ? T : F;
-  const int64_t rows = n1 > 1 ? (t * n1 < 3 * t + F ? t * n1 : 3 * t + F) : 0;
+  const int64_t most = prefill_most_splits(m), t = T < F ? T : F;
+  const int64_t rows = most > 1 && m.bh <= kPrefillFill ? (t * most < 2 * F ? t * most : 2 * F) : 0;
   w.part = take(m.bh * rows * w.part_stride * 4);
   w.total = w.total > off ? w.total : off;
   return w;

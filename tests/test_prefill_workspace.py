@@ -33,13 +33,22 @@ def test_records_fit(shape):
     bh, steps = b * hkv, k * (B // 32)
     fit = 16 if g <= 1 else 8 if g <= 2 else 4 if g <= 4 else 2  # positions per wavefront
 
-    def splits(t):
-        groups = bh * -(-t // (1 if bh * t * steps <= 16384 else fit))
-        most = min(-(-steps // 2), max(16, steps // 4), 32)
-        n = min(-(-2048 // groups), most)
-        if n > 2:  # the nearest multiple of four within most
-            n = (n + 2) // 4 * 4 if (n + 2) // 4 * 4 <= most else 2 if n < 4 else n // 4 * 4
-        return n
+    n = (steps + 1) // 2
+    most = min(n if n <= 16 else max(16, steps // 4), 32)
+
+    def splits(t):  # the least rounds x (steps of ceil(k / n) blocks + 2)
+        ng, best = -(-t // (1 if bh * t * steps <= 16384 else fit)), None
+        for n in range(1, most + 1):
+            if n > 1 and bh * ng * n > 4096:
+                break
+            gw = 1 if n % 4 == 0 else 2 if n % 2 == 0 else 4
+            full, r = divmod(bh * -(-ng // gw) * gw * n, 2048)
+            last = (0 if r == 0 else (80 if r <= 1024 else 100) if full == 0
+                    else 70 if r <= 1024 else 85 if r < 1536 else 100)
+            cost = (100 * full + last) * (-(-k // n) * (B // 32) + 2)
+            if best is None or cost < best[0]:
+                best = cost, n
+        return best[1]
 
     row = (48 + 2 * g * d) * 4
     for T in (1, 2, 7, 31, 32, 33, 64, 100, 256, 1000):
