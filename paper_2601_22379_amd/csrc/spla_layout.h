@@ -284,7 +284,8 @@ SPLA_HD int prefill_most_splits(const Dims& m) {
 // little faster than two (half a round 0.8), and the ends of a first round fill with
 // a second (half a round 0.7, three quarters 0.85). 4 x 8 units at 128K, 8 positions:
 // 16 splits (1024 places) 127 us, 32 (2048) 97; 96 positions: 3 (2304) 768, 4 (3072)
-// 621; 8 units of 5 heads, 48 positions: 12 (2304) 82, 10 (1920) 69.
+// 621; 8 units of 5 heads, 48 positions: 12 (2304) 82, 10 (1920) 69. Of equals the
+// largest even one (lists longer than k: there 8 took 80).
 SPLA_HD int prefill_splits(const Dims& m, int T) {
   const int64_t ng = ceil_div(T, prefill_positions(m, T));
   const int most = prefill_most_splits(m), cpb = m.B / 32;
@@ -297,7 +298,7 @@ SPLA_HD int prefill_splits(const Dims& m, int T) {
     const bool any = w % kPrefillFill != 0, half = 2 * (w % kPrefillFill) <= kPrefillFill;
     const int64_t last = !any ? 0 : full == 0 ? (half ? 80 : 100) : half ? 70 : r < 3 ? 85 : 100;
     const int64_t cost = (100 * full + last) * (ceil_div(m.k, n) * cpb + 2);
-    if (n == 1 || cost < best_cost) {
+    if (n == 1 || cost < best_cost || (cost == best_cost && n % 2 == 0)) {
       best = n;
       best_cost = cost;
     }

@@ -46,7 +46,7 @@ def test_records_fit(shape):
             last = (0 if r == 0 else (80 if r <= 1024 else 100) if full == 0
                     else 70 if r <= 1024 else 85 if r < 1536 else 100)
             cost = (100 * full + last) * (-(-k // n) * (B // 32) + 2)
-            if best is None or cost < best[0]:
+            if best is None or cost < best[0] or (cost == best[0] and n % 2 == 0):
                 best = cost, n
         return best[1]
 
